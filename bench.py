@@ -38,13 +38,13 @@ VARIANTS = {
                     ["paper_2209_13121_amd/csrc/m2l_bf16.hip", "paper_2209_13121_amd/csrc/m2l_common.h",
                      "paper_2209_13121_amd/csrc/bf16_split.h", "paper_2209_13121_amd/csrc/fmm_internal.h"],
                     "f16", 3),
-    "mixed_f32": ("MIXED", "F32", "k_m2l<8,float>",
-                  ["paper_2209_13121_amd/csrc/m2l.hip", "paper_2209_13121_amd/csrc/m2l_common.h",
-                   "paper_2209_13121_amd/csrc/fmm_internal.h"],
+    "mixed_f32": ("MIXED", "F32", "k_m2l_block<8,float>",
+                  ["paper_2209_13121_amd/csrc/m2l_sym_kernel.h", "paper_2209_13121_amd/csrc/m2l_sym.h",
+                   "paper_2209_13121_amd/csrc/m2l_common.h", "paper_2209_13121_amd/csrc/fmm_internal.h"],
                   "f32", 1),
-    "fp64": ("FP64", "AUTO", "k_m2l<8,double>",
-             ["paper_2209_13121_amd/csrc/m2l.hip", "paper_2209_13121_amd/csrc/m2l_common.h",
-              "paper_2209_13121_amd/csrc/fmm_internal.h"],
+    "fp64": ("FP64", "AUTO", "k_m2l_block<8,double>",
+             ["paper_2209_13121_amd/csrc/m2l_sym_kernel.h", "paper_2209_13121_amd/csrc/m2l_sym.h",
+              "paper_2209_13121_amd/csrc/m2l_common.h", "paper_2209_13121_amd/csrc/fmm_internal.h"],
              "f64", 1),
 }
 HEADLINE = "mixed_f16x2"  # the mixed form the library picks for FMM_M2L_AUTO

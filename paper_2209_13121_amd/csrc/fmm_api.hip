@@ -6,7 +6,7 @@
 #include <algorithm>
 #include <new>
 
-#include "fmm_internal.h"
+#include "m2l_sym.h"
 
 namespace fmm {
 
@@ -186,6 +186,12 @@ void prof_end(fmm_plan_s* P, hipStream_t s) {
   P->prof_open = false;
   hipEventRecord(P->rec[P->nrec].stop, s);
   P->nrec++;
+}
+
+static hipError_t launch_m2l(fmm_plan_s* P, hipStream_t s) {
+  if (P->m2l_np) return launch_m2l_bf16(P, s);
+  if (!sym::serves(P->p)) return launch_m2l_plain(P, s);
+  return P->mixed ? launch_m2l_sym_f32(P, s) : launch_m2l_sym_f64(P, s);
 }
 
 // Every pass before the near field: upward, M2L (+ P2L on the adaptive tree),

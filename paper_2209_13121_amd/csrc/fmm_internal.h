@@ -286,8 +286,8 @@ hipError_t fill_u32(uint32_t* a, int64_t n, uint32_t v, hipStream_t s);  // a[0.
 hipError_t launch_tree(fmm_plan_s* P, const double* d_pos, hipStream_t s);
 hipError_t launch_operators(fmm_plan_s* P, hipStream_t s);
 hipError_t launch_upward(fmm_plan_s* P, const double* d_q, hipStream_t s);
-hipError_t launch_m2l(fmm_plan_s* P, hipStream_t s);
-hipError_t launch_m2l_bf16(fmm_plan_s* P, hipStream_t s);  // split-BF16 form (P->m2l_np > 0)
+hipError_t launch_m2l_plain(fmm_plan_s* P, hipStream_t s);  // FP32 / FP64, p <= 3
+hipError_t launch_m2l_bf16(fmm_plan_s* P, hipStream_t s);  // split forms (P->m2l_np > 0)
 hipError_t launch_m2m(fmm_plan_s* P, hipStream_t s);
 hipError_t launch_l2l(fmm_plan_s* P, hipStream_t s);
 hipError_t launch_downward(fmm_plan_s* P, hipStream_t s);

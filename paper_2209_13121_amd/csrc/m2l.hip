@@ -1,4 +1,5 @@
-// m2l.hip -- multipole-to-local translation on the matrix cores.
+// m2l.hip -- multipole-to-local translation on the FP32 / FP64 matrix cores up
+// to p = 3 (one 16-row block; higher orders: m2l_sym.h).
 //
 // For a target box t at level l >= 2 the interaction list is every box s of
 // level l whose parent is adjacent to t's parent but which is not adjacent to
@@ -378,10 +379,15 @@ struct M2LRun {
 
 }  // namespace
 
-hipError_t launch_m2l(fmm_plan_s* P, hipStream_t s) {
-  if (P->m2l_np) return launch_m2l_bf16(P, s);  // times its split and M2L kernels apart
+hipError_t launch_m2l_plain(fmm_plan_s* P, hipStream_t s) {
   prof_begin(P, FMM_PHASE_M2L, s);
-  hipError_t e = dispatch_p<M2LRun>(P->p, P, s);
+  hipError_t e = hipErrorInvalidValue;
+  switch (P->p) {
+    case 0: e = M2LRun<0>::run(P, s); break;
+    case 1: e = M2LRun<1>::run(P, s); break;
+    case 2: e = M2LRun<2>::run(P, s); break;
+    case 3: e = M2LRun<3>::run(P, s); break;
+  }
   prof_end(P, s);
   return e;
 }

@@ -1,5 +1,5 @@
 // m2l_common.h -- work decomposition shared by the M2L kernels (FP32/FP64
-// MFMA in m2l.hip, split-BF16 MFMA in m2l_bf16.hip).
+// MFMA in m2l.hip and m2l_sym_kernel.h, split MFMA in m2l_bf16.hip).
 //
 // For a target box t at level l >= 2 the interaction list is every box s of
 // level l whose parent is adjacent to t's parent but which is not adjacent to
@@ -89,7 +89,7 @@ struct Args {
   int64_t vt_off[FMM_DEPTH_MAX + 2];
 };
 
-inline Args make_args(fmm_plan_s* Pl) {
+inline Args make_args(fmm_plan_s* Pl, int targets = kTargetsPerGroup) {
   const Layout& lay = Pl->lay;
   Args a;
   a.L = Pl->adaptive ? Pl->Ld : Pl->L;
@@ -101,7 +101,7 @@ inline Args make_args(fmm_plan_s* Pl) {
   for (int l = 2; l <= a.L; ++l) {
     a.group_off[l] = g;
     const int64_t np = Pl->adaptive ? Pl->nsplit[l - 1] : (int64_t)1 << (3 * (l - 1));
-    g += 8 * ((np + kTargetsPerGroup - 1) / kTargetsPerGroup);
+    g += 8 * ((np + targets - 1) / targets);
   }
   a.group_off[a.L + 1] = g;
   a.ngroups = g;

@@ -18,10 +18,11 @@
 // M2L is applied when its result is promoted (L2L pass).
 //
 // Tables, zero padded: M2M and L2L, 8 octants each, FP64, stored
-// [octant][input k (padded to KP)][output row (padded to RP)]; M2L, 316
-// offsets in the M2L precision, stored [offset][output row (padded to RP)]
-// [input k (stride m2l_kstride_of)].
+// [octant][input k (padded to KP)][output row (padded to RP)]; M2L in the
+// order of its form's kernel (m2l_sym.h; bf16_split.h, fmm_internal.h m2lb_*
+// and m2lw_*).
 #include "bf16_split.h"
+#include "m2l_sym.h"
 
 namespace fmm {
 namespace {
@@ -230,6 +231,34 @@ __global__ void k_gen_m2l(int p, int rp, int ks, T* __restrict__ ops) {
   }
 }
 
+// Reflection-reduced M2L: one operator per orbit of offsets (m2l_sym.h), in
+// the order its products read: [chunk][16-row block][lane][k step of the
+// chunk], lane = 16 (column group) + row.  kSymSplit blocks per operator, each
+// a range of its entries.
+constexpr int kSymSplit = 8;
+template <typename T>
+__global__ void k_gen_m2l_sym(int p, sym::Tab tab, int op_elems, T* __restrict__ ops) {
+  __shared__ double tre[kTabMax], tim[kTabMax];
+  const int op = blockIdx.x / kSymSplit, part = blockIdx.x % kSymSplit;
+  if ((int)threadIdx.x <= 2 * p) {
+    int o[3];
+    sym::op_offset(op, o);
+    // o is the target-minus-source offset (c_t - c_s)/h
+    irregular_column((double)o[0], (double)o[1], (double)o[2], 2 * p, threadIdx.x, tre, tim);
+  }
+  __syncthreads();
+  const int v = 16 / (int)sizeof(T), ncol = 4 * (((p + 1) * (p + 1) + 3) / 4);
+  T* out = ops + (size_t)op * op_elems;
+  const int per = (op_elems + kSymSplit - 1) / kSymSplit, e0 = part * per;
+  const int e1 = e0 + per < op_elems ? e0 + per : op_elems;
+  for (int e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+    const int s = e % v, lane = e / v % 64, b = e / (v * 64) % tab.nb, ch = e / (v * 64 * tab.nb);
+    const int r = 4 * (ch * v + s) + lane / 16;  // column rank
+    const int row = tab.rcoef[16 * b + lane % 16], col = r < ncol ? tab.kcoef[r] : -1;
+    out[e] = (T)(row >= 0 && col >= 0 ? m2l_entry(p, row, col, tre, tim) : 0.0);
+  }
+}
+
 // Operators in pieces, in the chunked LDS layout of the split-BF16 M2L: one
 // thread per (operator row, k step, lane group) computes its 8 FP64 entries
 // and writes their NP quads.  Pad quads are zeroed beforehand.
@@ -427,6 +456,15 @@ hipError_t launch_operators(fmm_plan_s* P, hipStream_t s) {
       k_gen_m2l_bf<2><<<kNumM2LOps, kBlock, 0, s>>>(P->p, P->adaptive, ob);
     else
       k_gen_m2l_bf<3><<<kNumM2LOps, kBlock, 0, s>>>(P->p, P->adaptive, ob);
+  } else if (sym::serves(P->p)) {
+    const sym::Tab tab = sym::make_tab(P->p);
+    const unsigned grid = sym::kNumOps * kSymSplit;
+    if (P->mixed)
+      k_gen_m2l_sym<float><<<grid, kBlock, 0, s>>>(P->p, tab, (int)sym::op_elems(P->p, 4),
+                                                   wsp<float>(P, lay.op_m2l32));
+    else
+      k_gen_m2l_sym<double><<<grid, kBlock, 0, s>>>(P->p, tab, (int)sym::op_elems(P->p, 8),
+                                                    wsp<double>(P, lay.op_m2l64));
   } else if (P->mixed)
     k_gen_m2l<float><<<kNumM2LOps, kBlock, 0, s>>>(P->p, rp, m2l_kstride_of(P->nc, 4),
                                                    wsp<float>(P, lay.op_m2l32));
