@@ -8,22 +8,20 @@
 // offset from t's centre in t's box units,
 // s_j = o_c + sc_c u_j (o_c the source leaf's centre offset, sc_c its size in
 // t's units, u_j the particle's offset in its own leaf, all exact in FP64),
-// then every lane reads the tile:
-//   * T <= 32 targets: lane = t + T' g (T' the power of two >= T, G = 64 / T'
-//     groups); group g takes sources g, g + G, ... of each tile, and the
-//     groups' sums are combined by xor shuffles over the lane bits of g, in a
-//     fixed order;
-//   * T > 32: every lane holds K = ceil(T / 64) <= kKMax targets (lane +
-//     64 m) and reads every source of the tile (one LDS broadcast read
-//     serves K pairs); leaves above 64 kKMax targets run in groups.
-// Mixed precision: s_j and the target's u_i are carried as FP32 pairs
-// hi + lo (hi = fp32(x), lo = fp32(x - hi)), so the pair offset
-// (u_hi - s_hi) + (u_lo - s_lo) keeps FP32 relative accuracy however close
-// the pair; r^2, 1/r and the sums run in FP32.  FP64: the offset u_i - s_j in
-// FP64.  The target's own leaf is staged first: its pairs at distance 0 (the
-// target itself, or a coincident point, which always shares the leaf)
-// contribute nothing, and more than one per target raises the coincident
-// flag; pairs with the other leaves skip that check.
+// then the leaf's targets take the tile in groups (target_group):
+//   * whole sets of 64 targets: every lane holds K <= kKMax of them (lane + 64
+//     m) and reads every source (one LDS broadcast read serves K pairs);
+//   * the remaining r < 64: L = ceil(r / K) lanes hold K targets each and G =
+//     64 / L copies of them split the sources (copy g takes sources g, g + G,
+//     ... of the leaf's list), K chosen for the fullest wave; the copies' sums
+//     are combined by shuffles, halving G, in a fixed order.
+// Pair offsets u_i - s_j are taken in FP64 in both precisions (one instruction
+// an axis: the FP64 vector rate is the FP32 one); mixed rounds them to FP32,
+// so they keep FP32 relative accuracy however close the pair, and r^2, 1/r and
+// the sums run in FP32.  The target's own leaf is staged first: its pairs at
+// distance 0 (the target itself, or a coincident point, which always shares
+// the leaf) contribute nothing, and more than one per target raises the
+// coincident flag; pairs with the other leaves skip that check.
 // Then phi_i = phi_near + phi_far, F_i = -q_i grad phi_i (FP64), written at
 // the particle's user index.  In the adjoint form the same pass writes
 // g dE/dq_i = g phi_i and g dE/dx_i = g q_i grad phi_i: with every
@@ -31,6 +29,16 @@
 // quadratic form in q, and while no particle crosses a box face its gradient
 // in x_i is q_i grad phi_i.  E = 1/2 sum q_i phi_i is reduced in FP64 in a
 // fixed tree order over the per-particle terms.
+//
+// Bound: vector issue.  A mixed pair is 17 instructions (3 FP64 subtractions,
+// 3 conversions, 1 / r at half rate) and the loop adds 0.75 at K = 4: 81 cycles
+// for 64 pairs.  Measured (uniform): 2^20 charges, depth 4 (256 a leaf), mixed
+// 3.87 ms where 81 cycles for every pair would take 3.4 (FP32 hi + lo pair
+// offsets and a lane layout of one target per lane up to 32 targets, K = 1, 2,
+// 4 above: 4.65 ms), FP64 5.8 ms (1 / sqrt by square root and division, 2 waves
+// per SIMD: 13.9 ms); 10^5 charges, depth 4 (24 a leaf), mixed 96 -> 67 us;
+// 4096 charges, depth 3, FP64 125 -> 15 us (a wave per leaf instead of one per
+// parent box: 512 waves instead of 64).
 #include <math.h>
 
 #include <type_traits>
@@ -42,33 +50,21 @@ namespace {
 
 constexpr int kTile = 256;   // sources per staged tile (FMM_SCHED_P2P_TILE: 128, 256, 512)
 constexpr int kNbBatch = 64;  // neighbour leaves handled per batch (one per lane)
-constexpr int kKMax = 4;      // targets per lane of a large leaf (groups of 64 kKMax targets)
-// occupancy the register budget is held to: FP32 4 waves per SIMD (128 VGPRs),
-// FP64 2 (its targets and sums take twice the registers)
+constexpr int kKMax = 4;      // targets per lane, at most
+// occupancy the register budget is held to (waves per SIMD)
 template <typename T>
-constexpr int waves_per_simd() { return sizeof(T) == 4 ? 4 : 2; }
+constexpr int waves_per_simd() { return sizeof(T) == 4 ? 4 : 3; }
 
-// Staged source: mixed, {s_hi, q} and {s_lo, unused}; FP64, {s, q}.
+// Staged source: its offset from the target leaf's centre (box units) and its
+// charge.
 template <typename T>
-struct SSrc;
-template <>
-struct SSrc<float> {
-  float4 hq, lo;
-};
-template <>
-struct SSrc<double> {
-  double x, y, z, q;
+struct alignas(16) SSrc {
+  double x, y, z;
+  T q;
 };
 
 // A target in registers: its offset from its leaf centre (box units).
-template <typename T>
-struct Tgt;
-template <>
-struct Tgt<float> {
-  float xh, yh, zh, xl, yl, zl;
-};
-template <>
-struct Tgt<double> {
+struct Tgt {
   double x, y, z;
 };
 
@@ -78,28 +74,18 @@ struct Acc {
   int nz;  // pairs at distance 0 (the target itself included)
 };
 
-__device__ __forceinline__ void split2(double v, float& hi, float& lo) {
-  hi = (float)v;
-  lo = (float)(v - (double)hi);
-}
-
-template <typename T>
-__device__ __forceinline__ Tgt<T> make_tgt(const Rec<double>& r);
-template <>
-__device__ __forceinline__ Tgt<float> make_tgt<float>(const Rec<double>& r) {
-  Tgt<float> t;
-  split2(r.x, t.xh, t.xl);
-  split2(r.y, t.yh, t.yl);
-  split2(r.z, t.zh, t.zl);
-  return t;
-}
-template <>
-__device__ __forceinline__ Tgt<double> make_tgt<double>(const Rec<double>& r) {
-  return Tgt<double>{r.x, r.y, r.z};
-}
+__device__ __forceinline__ Tgt make_tgt(const Rec<double>& r) { return Tgt{r.x, r.y, r.z}; }
 
 __device__ __forceinline__ float inv_sqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double inv_sqrt(double x) { return 1.0 / sqrt(x); }
+// FP64: the hardware estimate y (about 2^-26) and one step of third order:
+// with e = 1 - x y^2, x^(-1/2) = y (1 + e / 2 + 3 e^2 / 8 + ...), the dropped
+// term below 2^-78; 6 instructions instead of the 30 of a square root and a
+// division (4 waves per SIMD instead of 2 as well).
+__device__ __forceinline__ double inv_sqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
 
 // One pair.  SELF: the source may be the target itself or coincide with it
 // (sources of the target's own leaf: coincident points share a leaf), so a
@@ -107,19 +93,8 @@ __device__ __forceinline__ double inv_sqrt(double x) { return 1.0 / sqrt(x); }
 // zero distance there would make the sums non-finite, which finish_particle
 // flags).
 template <typename T, bool SELF>
-__device__ __forceinline__ void pair(Acc<T>& a, const Tgt<T>& t, const SSrc<T>& s) {
-  T dx, dy, dz, q;
-  if constexpr (sizeof(T) == 4) {
-    dx = (t.xh - s.hq.x) + (t.xl - s.lo.x);
-    dy = (t.yh - s.hq.y) + (t.yl - s.lo.y);
-    dz = (t.zh - s.hq.z) + (t.zl - s.lo.z);
-    q = s.hq.w;
-  } else {
-    dx = t.x - s.x;
-    dy = t.y - s.y;
-    dz = t.z - s.z;
-    q = s.q;
-  }
+__device__ __forceinline__ void pair(Acc<T>& a, const Tgt& t, const SSrc<T>& s) {
+  const T dx = (T)(t.x - s.x), dy = (T)(t.y - s.y), dz = (T)(t.z - s.z), q = s.q;
   const T r2 = dx * dx + dy * dy + dz * dz;
   T rinv;
   if constexpr (SELF) {
@@ -261,37 +236,72 @@ struct AdaptiveNbs {
 };
 
 template <typename T>
-__device__ __forceinline__ SSrc<T> stage_one(const Rec<double>& r, const Nb& nb);
-template <>
-__device__ __forceinline__ SSrc<float> stage_one<float>(const Rec<double>& r, const Nb& nb) {
-  SSrc<float> s;
-  split2(fma(nb.sc, r.x, nb.ox), s.hq.x, s.lo.x);
-  split2(fma(nb.sc, r.y, nb.oy), s.hq.y, s.lo.y);
-  split2(fma(nb.sc, r.z, nb.oz), s.hq.z, s.lo.z);
-  s.hq.w = (float)r.q;
-  s.lo.w = 0.f;
-  return s;
-}
-template <>
-__device__ __forceinline__ SSrc<double> stage_one<double>(const Rec<double>& r, const Nb& nb) {
-  return SSrc<double>{fma(nb.sc, r.x, nb.ox), fma(nb.sc, r.y, nb.oy), fma(nb.sc, r.z, nb.oz), r.q};
+__device__ __forceinline__ SSrc<T> stage_one(const Rec<double>& r, const Nb& nb) {
+  return SSrc<T>{fma(nb.sc, r.x, nb.ox), fma(nb.sc, r.y, nb.oy), fma(nb.sc, r.z, nb.oz), (T)r.q};
 }
 
-// Pairs of K targets per lane (targets lane + 64 m) with sources [0, ns) of
-// the tile, the first nself of them from the target's own leaf.
+// Pairs of a lane's K targets with sources j0, j0 + G, .. < ns of the tile, the
+// first nself of them from the target's own leaf; returns the first j >= ns.
 template <typename T, int K>
-__device__ __forceinline__ void tile_big(Acc<T> (&acc)[kKMax], const Tgt<T> (&tg)[kKMax], const SSrc<T>* sS,
-                                         int nself, int ns) {
-  for (int j = 0; j < nself; ++j) {
+__device__ __forceinline__ int tile_pairs(Acc<T> (&acc)[kKMax], const Tgt (&tg)[kKMax], const SSrc<T>* sS, int j0,
+                                           int G, int nself, int ns) {
+  int j = j0;
+  for (; j < nself; j += G) {
     const SSrc<T> s = sS[j];
 #pragma unroll
     for (int m = 0; m < K; ++m) pair<T, true>(acc[m], tg[m], s);
   }
-  for (int j = nself; j < ns; ++j) {
+  for (; j < ns; j += G) {
     const SSrc<T> s = sS[j];
 #pragma unroll
     for (int m = 0; m < K; ++m) pair<T, false>(acc[m], tg[m], s);
   }
+  return j;
+}
+
+// How the next targets of a leaf (rem of them left) lie over the wave: n
+// targets, K per lane, L lanes per copy, G copies.  For the last rem < 64 the
+// K of the fewest instructions for 27 rem sources: 20 K + 6 per source of a
+// copy, 20 K per round of the combination (24 targets: 2 x 12 lanes x 5 copies,
+// 94 % of the lanes busy, against 75 % for 24 x 2).
+struct Group {
+  int n, K, L, G;
+};
+// K | L << 3 | G << 10 | ceil(2^14 / L) << 17 for rem = 1 .. 63
+struct GroupTable {
+  uint32_t v[64];
+};
+constexpr GroupTable make_groups() {
+  GroupTable t{};
+  for (int rem = 1; rem < 64; ++rem) {
+    int least = 1 << 30;
+    for (int K = 1; K <= kKMax; ++K) {
+      const int L = (rem + K - 1) / K, G = 64 / L;
+      int rounds = 0;
+      while ((1 << rounds) < G) ++rounds;
+      const int cost = (27 * rem + G - 1) / G * (20 * K + 6) + 20 * K * rounds;
+      if (cost < least) {
+        least = cost;
+        t.v[rem] = (uint32_t)(K | L << 3 | G << 10 | ((1 << 14) + L - 1) / L << 17);
+      }
+    }
+  }
+  return t;
+}
+static __constant__ GroupTable kGroups = make_groups();
+// The next group, and this lane's copy gi and first target tl in it
+__device__ __forceinline__ Group target_group(int rem, int lane, int& gi, int& tl) {
+  if (rem >= 64) {
+    const int K = rem / 64 < kKMax ? rem / 64 : kKMax;
+    gi = 0;
+    tl = lane;
+    return Group{64 * K, K, 64, 1};
+  }
+  const uint32_t c = kGroups.v[rem];
+  const Group g{rem, (int)(c & 7u), (int)(c >> 3 & 127u), (int)(c >> 10 & 127u)};
+  gi = (int)((uint32_t)lane * (c >> 17) >> 14);  // lane / L, exact for lane < 64
+  tl = lane - gi * g.L;
+  return g;
 }
 
 // LDS of one wave's leaf (TILE sources per staged tile).
@@ -314,26 +324,19 @@ __device__ __forceinline__ void p2p_leaf(const NBS& nbs, int64_t b, P2PShared<T,
   uint32_t t0, nt;
   int lt;
   if (!nbs.target(b, t0, nt, lt)) return;  // uniform over the wave
-  // target layout: small leaves split the sources over lane groups, large
-  // ones take up to kKMax targets per lane, in groups of 64 kKMax targets
-  // (each group stages the sources again)
-  const bool small = nt <= 32;
-  int tp = 1;
-  while (tp < (int)nt) tp <<= 1;
-  const int G = small ? 64 / tp : 1;
-  const int gi = small ? lane / tp : 0;  // source group of this lane
   const int nn = nbs.count(b);
+  const double inv_h = (double)(1 << lt) / dp->side;
   Acc<T> acc[kKMax];
-  Tgt<T> tg[kKMax];
-  constexpr uint32_t kGrp = 64 * kKMax;
-  for (uint32_t g0 = 0; g0 < nt; g0 += kGrp) {
-    const int ng = (int)(nt - g0 < kGrp ? nt - g0 : kGrp);  // targets of this group
-    const int K = small ? 1 : (ng + 63) / 64;               // targets per lane
+  Tgt tg[kKMax];
+  for (uint32_t g0 = 0; g0 < nt;) {
+    int gi, tl;  // this lane's copy and first target
+    const Group gr = target_group((int)__builtin_amdgcn_readfirstlane((int)(nt - g0)), lane, gi, tl);
+    const int K = gr.K, G = gr.G;
 #pragma unroll
     for (int m = 0; m < kKMax; ++m) {
       acc[m] = Acc<T>{T(0), T(0), T(0), T(0), 0};
-      const int t = small ? lane % tp : lane + 64 * m;
-      if (m < K) tg[m] = make_tgt<T>(src[t0 + g0 + (t < ng ? t : 0)]);
+      const int t = tl + gr.L * m;
+      if (m < K) tg[m] = make_tgt(src[t0 + g0 + (t < gr.n ? t : 0)]);
     }
     for (int n0 = 0; n0 < nn; n0 += kNbBatch) {
       // neighbour batch: one leaf per lane, the inclusive scan of counts
@@ -352,6 +355,7 @@ __device__ __forceinline__ void p2p_leaf(const NBS& nbs, int64_t b, P2PShared<T,
       if (lane == 0) sPre[0] = 0;
       const uint32_t total = __shfl(c, 63, 64);
       __syncthreads();
+      int first = gi;  // this copy's first source in the tile
       for (uint32_t c0 = 0; c0 < total; c0 += TILE) {
         const int ns = (int)(total - c0 < (uint32_t)TILE ? total - c0 : (uint32_t)TILE);
         // stage: lane stages sources c0 + lane + 64 m of the batch
@@ -372,38 +376,47 @@ __device__ __forceinline__ void p2p_leaf(const NBS& nbs, int64_t b, P2PShared<T,
         // the target leaf's own sources lead batch 0 (neighbour 0)
         int nself = 0;
         if (n0 == 0 && c0 < nt) nself = nt - c0 < (uint32_t)ns ? (int)(nt - c0) : ns;
-        if (small) {
-          int j = gi;
-          for (; j < nself; j += G) pair<T, true>(acc[0], tg[0], sS[j]);
-          for (; j < ns; j += G) pair<T, false>(acc[0], tg[0], sS[j]);
-        } else if (K == 1) {
-          tile_big<T, 1>(acc, tg, sS, nself, ns);
-        } else if (K == 2) {
-          tile_big<T, 2>(acc, tg, sS, nself, ns);
-        } else {
-          tile_big<T, kKMax>(acc, tg, sS, nself, ns);
-        }
+        // copy gi takes the batch's sources c0 + j = gi modulo G (whatever the
+        // tile); the lanes past the last copy none
+        const int j0 = gi >= G ? ns : first;
+        int last = j0;
+        if (K == 1)
+          last = tile_pairs<T, 1>(acc, tg, sS, j0, G, nself, ns);
+        else if (K == 2)
+          last = tile_pairs<T, 2>(acc, tg, sS, j0, G, nself, ns);
+        else if (K == 3)
+          last = tile_pairs<T, 3>(acc, tg, sS, j0, G, nself, ns);
+        else
+          last = tile_pairs<T, kKMax>(acc, tg, sS, j0, G, nself, ns);
+        first = last - ns;  // past this tile's end, within the next
         __syncthreads();
       }
     }
-    if (!small) {
-      const double inv_h = (double)(1 << lt) / dp->side;
+    // the copies' sums: the upper half's onto the lower half's, until one is left
+    for (int g = G; g > 1; g = (g + 1) / 2) {
+      const int h = (g + 1) / 2, from = lane + gr.L * h;
+      const bool take = gi + h < g;
 #pragma unroll
-      for (int m = 0; m < kKMax; ++m)
-        if (m < K && lane + 64 * m < ng)
-          finish_particle<T>(fa, (int64_t)t0 + g0 + lane + 64 * m, inv_h, acc[m]);
+      for (int m = 0; m < kKMax; ++m) {
+        if (m >= K) break;
+        const T f = __shfl(acc[m].f, from, 64), gx = __shfl(acc[m].gx, from, 64);
+        const T gy = __shfl(acc[m].gy, from, 64), gz = __shfl(acc[m].gz, from, 64);
+        const int nz = __shfl(acc[m].nz, from, 64);
+        if (take) {
+          acc[m].f += f;
+          acc[m].gx += gx;
+          acc[m].gy += gy;
+          acc[m].gz += gz;
+          acc[m].nz += nz;
+        }
+      }
     }
+#pragma unroll
+    for (int m = 0; m < kKMax; ++m)
+      if (m < K && gi == 0 && tl + gr.L * m < gr.n)
+        finish_particle<T>(fa, (int64_t)t0 + g0 + tl + gr.L * m, inv_h, acc[m]);
+    g0 += gr.n;
   }
-  if (!small) return;
-  // small leaf: the G groups' sums, combined by xor shuffles over the group bits
-  for (int w = tp; w < 64; w <<= 1) {
-    acc[0].f += __shfl_xor(acc[0].f, w, 64);
-    acc[0].gx += __shfl_xor(acc[0].gx, w, 64);
-    acc[0].gy += __shfl_xor(acc[0].gy, w, 64);
-    acc[0].gz += __shfl_xor(acc[0].gz, w, 64);
-    acc[0].nz += __shfl_xor(acc[0].nz, w, 64);
-  }
-  if (lane < (int)nt) finish_particle<T>(fa, (int64_t)t0 + lane, (double)(1 << lt) / dp->side, acc[0]);
 }
 
 // One wave per box (boxes that are no leaf, or empty, return at once).
@@ -506,6 +519,7 @@ __global__ void k_p2p_worklist(int64_t nbox, const uint8_t* __restrict__ bucket,
 // SIMD); tiles of 512 held all 64 leaves of a typical block at once but
 // limited it to 9 waves per CU: 0.37 -> 0.26 ms at 2^20 charges, depth 6.
 constexpr int kGroupTile = 256;
+constexpr int64_t kGroupParents = 4096;  // fewer leave SIMDs without a wave: a wave per leaf then
 template <typename T>
 __global__ __launch_bounds__(64, waves_per_simd<T>()) void k_p2p_group(
     int L, const uint32_t* __restrict__ start, const uint32_t* __restrict__ c2s,
@@ -563,7 +577,7 @@ __global__ __launch_bounds__(64, waves_per_simd<T>()) void k_p2p_group(
     r.x += (double)lx - 1.5;
     r.y += (double)ly - 1.5;
     r.z += (double)lz - 1.5;
-    const Tgt<T> tg = make_tgt<T>(r);
+    const Tgt tg = make_tgt(r);
     const int kown = 16 * lx + 4 * ly + lz;
     Acc<T> acc = {T(0), T(0), T(0), T(0), 0};
     for (uint32_t c0 = 0; c0 < total; c0 += kGroupTile) {
@@ -737,9 +751,9 @@ hipError_t launch_near_and_finish(fmm_plan_s* P, double* d_phi, double* d_force,
     UniformNbs nb{L, wsp<uint32_t>(P, lay.leaf_start), wsp<uint32_t>(P, lay.coord2slot) + lay.lvl_off[L],
                   wsp<uint32_t>(P, lay.slot2coord) + lay.lvl_off[L]};
     const int64_t nleaf = lay.nleaf;
-    if (L >= 1 && n <= 8 * nleaf) {
+    const int64_t npar = nleaf / 8;
+    if (npar >= kGroupParents && n <= 8 * nleaf) {
       // small leaves (at most 8 particles on average): a wave per parent box
-      const int64_t npar = nleaf / 8;
       const uint32_t* sl = wsp<uint32_t>(P, lay.sorted_leaf);
       if (P->mixed)
         k_p2p_group<float><<<(unsigned)npar, 64, 0, s>>>(L, nb.start, nb.c2s, nb.s2c, sl, dp, src, fa);
