@@ -34,7 +34,7 @@
 
 #include <algorithm>
 
-#include "fmm_internal.h"
+#include "p2m.h"
 #include "m2l_common.h"
 
 namespace fmm {
@@ -458,68 +458,13 @@ __device__ __forceinline__ void irregular_harmonics_each(T x, T y, T z, F&& f) {
 
 // P2M at the leaves of levels >= 2, accumulated in FP64 from the FP64
 // offsets (as in the uniform pass); the mixed mode also stores it in FP32.
-template <int P>
+template <int P, int G>
 __global__ __launch_bounds__(64) void k_p2m_adaptive(ATree t, const Rec<double>* __restrict__ src,
                                                      double* __restrict__ mult64, float* __restrict__ mult32) {
-  typedef double T;
-  constexpr int NC = (P + 1) * (P + 1);
-  constexpr int MS = mstride_of(NC);
-  constexpr int NT = (P + 1) * (P + 2) / 2;
-  const int64_t b = t.ce_off[2] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= t.nbox || t.child0[b] >= 0) return;
-  T acc[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) acc[c] = T(0);
+  const int64_t b = t.ce_off[2] + (int64_t)blockIdx.x * (64 / G) + threadIdx.x / G;
+  if (b >= t.nbox || t.child0[b] >= 0) return;  // the whole group
   const uint32_t s0 = t.range[2 * b], s1 = s0 + t.range[2 * b + 1];
-  for (uint32_t s = s0; s < s1; ++s) {
-    T re[NT], im[NT];
-    const Rec<T> r = src[s];
-    regular_harmonics<P, T>(r.x, r.y, r.z, re, im);
-    const T qq = r.q;
-#pragma unroll
-    for (int nn = 0; nn <= P; ++nn) {
-      acc[cidx_re(nn, 0)] += qq * re[tri(nn, 0)];
-#pragma unroll
-      for (int m = 1; m <= nn; ++m) {
-        acc[cidx_re(nn, m)] += qq * re[tri(nn, m)];
-        acc[cidx_im(nn, m)] -= qq * im[tri(nn, m)];
-      }
-    }
-  }
-  double* out = mult64 + b * MS;
-#pragma unroll
-  for (int c = 0; c < MS; ++c) out[c] = c < NC ? acc[c] : T(0);
-  if (mult32) {
-    float* o32 = mult32 + b * MS;
-#pragma unroll
-    for (int c = 0; c < MS; ++c) o32[c] = c < NC ? (float)acc[c] : 0.f;
-  }
-}
-
-// Sum over the 64 lanes of a wave of N values per lane (N a power of two,
-// >= 64), by halving: at each step the lanes exchange half of what they still
-// hold with the partner lane w apart, the lanes with bit w set keeping the
-// upper half.  Afterwards lane L holds in v[0 .. N/64) the sums of the values
-// N/64 L .. N/64 L + N/64 - 1.  N - 2 shuffles instead of 6 N, in a fixed order.
-template <int H, int W, typename T>
-__device__ __forceinline__ void halve_exchange(T* v) {
-  const bool up = (threadIdx.x & W) != 0;
-#pragma unroll
-  for (int i = 0; i < H; ++i) {
-    const T send = up ? v[i] : v[i + H];
-    const T keep = up ? v[i + H] : v[i];
-    v[i] = keep + __shfl_xor(send, W);
-  }
-}
-template <int N, typename T>
-__device__ __forceinline__ void wave_sum_split(T* v) {
-  static_assert(N >= 64 && (N & (N - 1)) == 0, "N must be a power of two >= 64");
-  halve_exchange<N / 2, 32>(v);
-  halve_exchange<N / 4, 16>(v);
-  halve_exchange<N / 8, 8>(v);
-  halve_exchange<N / 16, 4>(v);
-  halve_exchange<N / 32, 2>(v);
-  halve_exchange<N / 64, 1>(v);
+  p2m_box<P, G>(src, s0, s1, threadIdx.x % G, b, mult64, mult32);
 }
 
 // Coefficients of degree <= p whose order m lies in [m0, m1), in the order of
@@ -557,7 +502,7 @@ __host__ __device__ constexpr int orders_split(int p) {
 // One wave per box of the compact list xbox (the boxes whose X list is not
 // empty).  The lanes take the (X entry, particle) pairs of the list in order,
 // 64 at a time, so a short leaf does not leave lanes idle; each lane keeps its
-// own partial expansion, and the wave sums them at the end (wave_sum_split).
+// own partial expansion, and the wave sums them at the end (group_sum_split).
 template <int P, typename T, int M0, int M1>
 __global__ __launch_bounds__(64) void k_p2l(ATree t, const uint32_t* __restrict__ xbox,
                                             const uint32_t* __restrict__ xoff,
@@ -608,7 +553,7 @@ __global__ __launch_bounds__(64) void k_p2l(ATree t, const uint32_t* __restrict_
           });
     }
   }
-  wave_sum_split<N>(acc);
+  group_sum_split<N, 64>(acc);
   // local index u -> global coefficient index
   T* o = m2l + b * NC;
 #pragma unroll
@@ -762,9 +707,15 @@ struct P2MAdaptiveRun {
     const ATree t = tree_view(Pl);
     const int64_t nb = t.nbox - t.ce_off[2];
     if (nb <= 0) return hipGetLastError();
-    k_p2m_adaptive<P><<<grid_for(nb, 64), 64, 0, s>>>(
-        t, wsp<Rec<double>>(Pl, Pl->mixed ? lay.src64 : lay.src), wsp<double>(Pl, lay.mult64),
-        Pl->mixed ? wsp<float>(Pl, lay.mult32) : nullptr);
+    // a box's particles vary too much for a mean to say more: 16 lanes beat 4 and
+    // 64 from leaf_max 32 (10^6 in clusters, p = 6: 58 / 36 / 87 us) to 128 (p = 8:
+    // 81 / 43 / 164); smaller leaves leave lanes of a 16-group without a particle
+    with_p2m_lanes(Pl->cfg.leaf_max < 16 ? 4 : 16, [&](auto g) {
+      constexpr int G = decltype(g)::value;
+      k_p2m_adaptive<P, G><<<grid_for(nb * G, 64), 64, 0, s>>>(
+          t, wsp<Rec<double>>(Pl, Pl->mixed ? lay.src64 : lay.src), wsp<double>(Pl, lay.mult64),
+          Pl->mixed ? wsp<float>(Pl, lay.mult32) : nullptr);
+    });
     return hipGetLastError();
   }
 };

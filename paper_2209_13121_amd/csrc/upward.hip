@@ -1,7 +1,7 @@
 // upward.hip -- charges into Hilbert order, P2M at the leaves, M2M up to
 // level 2.
 //
-// P2M: M~_n^m = sum_j q_j conj(R_n^m(u_j)) with u_j the box-unit offset of
+// P2M (p2m.h): M~_n^m = sum_j q_j conj(R_n^m(u_j)) with u_j the box-unit offset of
 // particle j from its leaf centre (computed by the tree pass), accumulated in
 // FP64 in both precision modes from the FP64 offsets.  (An FP32 sum of
 // neutral clusters of charges, one cluster after another, rounds every
@@ -14,7 +14,7 @@
 // M2M (shift.hip): M~p = sum over the 8 children of A[octant] M~c with the
 // level-free octant matrices, always in FP64; in the mixed mode each parent is
 // also stored rounded to FP32 for the M2L pass.
-#include "fmm_internal.h"
+#include "p2m.h"
 
 namespace fmm {
 namespace {
@@ -31,45 +31,28 @@ __global__ void k_gather_q(const double* __restrict__ q, const int32_t* __restri
   if (src64) src64[s].q = v;
 }
 
-template <int P>
-__global__ __launch_bounds__(kBlock) void k_p2m(const uint32_t* __restrict__ start,
-                                                const Rec<double>* __restrict__ src, int64_t nleaf,
-                                                double* __restrict__ mult, float* __restrict__ mult32) {
-  typedef double T;
-  constexpr int NC = (P + 1) * (P + 1);
-  constexpr int MS = mstride_of(NC);
-  constexpr int NT = (P + 1) * (P + 2) / 2;
-  const int64_t leaf = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (leaf >= nleaf) return;
-  T acc[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) acc[c] = T(0);
-  const uint32_t b = start[leaf], e = start[leaf + 1];
-  for (uint32_t s = b; s < e; ++s) {
-    T re[NT], im[NT];
-    const Rec<T> r = src[s];
-    regular_harmonics<P, T>(r.x, r.y, r.z, re, im);
-    const T qq = r.q;
-#pragma unroll
-    for (int nn = 0; nn <= P; ++nn) {
-      acc[cidx_re(nn, 0)] += qq * re[tri(nn, 0)];
-#pragma unroll
-      for (int m = 1; m <= nn; ++m) {
-        acc[cidx_re(nn, m)] += qq * re[tri(nn, m)];
-        acc[cidx_im(nn, m)] -= qq * im[tri(nn, m)];
-      }
-    }
-  }
-  if (mult) {
-    T* out = mult + leaf * MS;
-#pragma unroll
-    for (int c = 0; c < MS; ++c) out[c] = c < NC ? acc[c] : T(0);
-  }
-  if (mult32) {
-    float* o32 = mult32 + leaf * MS;
-#pragma unroll
-    for (int c = 0; c < MS; ++c) o32[c] = c < NC ? (float)acc[c] : 0.f;
-  }
+template <int P, int G>
+__global__ __launch_bounds__(64) void k_p2m(const uint32_t* __restrict__ start,
+                                            const Rec<double>* __restrict__ src, int64_t nleaf,
+                                            double* __restrict__ mult64, float* __restrict__ mult32) {
+  const int64_t leaf = (int64_t)blockIdx.x * (64 / G) + threadIdx.x / G;
+  if (leaf >= nleaf) return;  // the whole group
+  p2m_box<P, G>(src, start[leaf], start[leaf + 1], threadIdx.x % G, leaf, mult64, mult32);
+}
+
+// Lanes per leaf: one for the smallest leaves (2^20 particles, depth 6, 4 per
+// leaf, p = 8: 1 / 2 / 4 lanes 49 / 52 / 62 us; p = 10: 84 / 96 / 129), then about a
+// quarter of the mean leaf up to 16 (200 001, depth 5, 6 per leaf, p = 12: 61 / 41 /
+// 45; 2^20, depth 5, 32 per leaf, p = 8: 55 / 41 / 27 and 8 lanes 27, 16 37; depth 4,
+// 256 per leaf: 16 / 32 / 64 lanes 26 / 30 / 40), and more where that leaves SIMDs
+// without a wave (4096 leaves of 24: 4 / 16 lanes 12.8 / 9.6 us; 512 leaves of
+// 2048: 16 / 64 lanes 120 / 38).
+int p2m_lanes(int64_t n, int64_t nleaf) {
+  constexpr int64_t kSimds = 1024;
+  int g = n >= 64 * nleaf ? 16 : (n >= 16 * nleaf ? 4 : (n >= 6 * nleaf ? 2 : 1));
+  if (nleaf * g < 64 * kSimds) g = 16;
+  if (nleaf * g < 64 * kSimds) g = 64;
+  return g;
 }
 
 template <int P>
@@ -77,10 +60,13 @@ struct P2MRun {
   static hipError_t run(fmm_plan_s* Pl, hipStream_t s) {
     const Layout& lay = Pl->lay;
     const int64_t nleaf = lay.nleaf, row0 = lay.lvl_off[Pl->L] * mstride(Pl->p);
-    k_p2m<P><<<grid_for(nleaf, 64), 64, 0, s>>>(
-        wsp<uint32_t>(Pl, lay.leaf_start), wsp<Rec<double>>(Pl, Pl->mixed ? lay.src64 : lay.src), nleaf,
-        Pl->mixed ? nullptr : wsp<double>(Pl, lay.mult64) + row0,
-        Pl->mixed ? wsp<float>(Pl, lay.mult32) + row0 : nullptr);
+    with_p2m_lanes(p2m_lanes(Pl->n, nleaf), [&](auto g) {
+      constexpr int G = decltype(g)::value;
+      k_p2m<P, G><<<grid_for(nleaf * G, 64), 64, 0, s>>>(
+          wsp<uint32_t>(Pl, lay.leaf_start), wsp<Rec<double>>(Pl, Pl->mixed ? lay.src64 : lay.src), nleaf,
+          Pl->mixed ? nullptr : wsp<double>(Pl, lay.mult64) + row0,
+          Pl->mixed ? wsp<float>(Pl, lay.mult32) + row0 : nullptr);
+    });
     return hipGetLastError();
   }
 };
