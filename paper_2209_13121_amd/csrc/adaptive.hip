@@ -707,10 +707,7 @@ struct P2MAdaptiveRun {
     const ATree t = tree_view(Pl);
     const int64_t nb = t.nbox - t.ce_off[2];
     if (nb <= 0) return hipGetLastError();
-    // a box's particles vary too much for a mean to say more: 16 lanes beat 4 and
-    // 64 from leaf_max 32 (10^6 in clusters, p = 6: 58 / 36 / 87 us) to 128 (p = 8:
-    // 81 / 43 / 164); smaller leaves leave lanes of a 16-group without a particle
-    with_p2m_lanes(Pl->cfg.leaf_max < 16 ? 4 : 16, [&](auto g) {
+    with_p2m_lanes(p2m_lanes(Pl->n, nb), [&](auto g) {
       constexpr int G = decltype(g)::value;
       k_p2m_adaptive<P, G><<<grid_for(nb * G, 64), 64, 0, s>>>(
           t, wsp<Rec<double>>(Pl, Pl->mixed ? lay.src64 : lay.src), wsp<double>(Pl, lay.mult64),

@@ -11,8 +11,8 @@
 // full otherwise.  Alone, one lane per box -> now, us: 2^20 particles, depth 4
 // (4096 boxes), p = 8: 279 -> 26; depth 5: 55 -> 27; 262 144, depth 4, p = 8:
 // 83 -> 14; depth 5: 28 -> 21; 100 003, depth 4, p = 6: 30 -> 10; 4096, depth 3,
-// p = 4: 12 -> 6; adaptive, 10^6 particles in clusters, leaf_max 32, p = 6:
-// 158 -> 36; 3 10^5, leaf_max 64, p = 10: 520 -> 48.
+// p = 4: 12 -> 6; adaptive, p = 10: 300 000 in clusters, FP64: 114 -> 39; 3 10^6
+// mixed: 324 -> 302 (11 particles a box).
 #pragma once
 #include <type_traits>
 
@@ -90,6 +90,23 @@ __device__ __forceinline__ void p2m_box(const Rec<double>* __restrict__ src, uin
     for (int i = 0; i < R; ++i)
       if (R * G == MS || R * g + i < MS) o[i] = (float)acc[i];
   }
+}
+
+// Lanes per box for n particles in nbox boxes: one for the smallest (2^20
+// particles, depth 6, 4 per leaf, p = 8: 1 / 2 / 4 lanes 49 / 52 / 62 us), then a
+// third to a quarter of the mean box up to 16 (6 per leaf, 32 768 leaves, p = 12:
+// 61 / 41 / 45; adaptive, 8.3 per box, p = 8: 70 / 60 / 66; 13 per box, p = 10:
+// 1 / 2 / 4 / 16 lanes 114 / 60 / 39 / 54; 32 per leaf: 2 / 4 / 8 / 16 lanes 41 / 27 /
+// 27 / 37; 256 per leaf: 16 / 32 / 64 lanes 26 / 30 / 40), and more where that leaves
+// SIMDs without a wave (4096 leaves of 24: 4 / 16 lanes 12.8 / 9.6; adaptive, 6208
+// boxes of 23: 22 / 14; 512 leaves of 2048: 16 / 64 lanes 120 / 38; but 10 952 boxes
+// of 7: 4 / 16 lanes 10.5 / 13.4).
+inline int p2m_lanes(int64_t n, int64_t nbox) {
+  constexpr int64_t kFullLanes = 40000;
+  const int steps[5] = {1, 2, 4, 16, 64};
+  int k = n >= 64 * nbox ? 3 : (n >= 10 * nbox ? 2 : (n >= 6 * nbox ? 1 : 0));
+  while (k < 4 && nbox * steps[k] < kFullLanes) ++k;
+  return steps[k];
 }
 
 // Calls f(std::integral_constant<int, G>) for g = 1, 2, 4, 16 or 64 lanes per box.

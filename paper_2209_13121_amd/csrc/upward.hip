@@ -40,21 +40,6 @@ __global__ __launch_bounds__(64) void k_p2m(const uint32_t* __restrict__ start,
   p2m_box<P, G>(src, start[leaf], start[leaf + 1], threadIdx.x % G, leaf, mult64, mult32);
 }
 
-// Lanes per leaf: one for the smallest leaves (2^20 particles, depth 6, 4 per
-// leaf, p = 8: 1 / 2 / 4 lanes 49 / 52 / 62 us; p = 10: 84 / 96 / 129), then about a
-// quarter of the mean leaf up to 16 (200 001, depth 5, 6 per leaf, p = 12: 61 / 41 /
-// 45; 2^20, depth 5, 32 per leaf, p = 8: 55 / 41 / 27 and 8 lanes 27, 16 37; depth 4,
-// 256 per leaf: 16 / 32 / 64 lanes 26 / 30 / 40), and more where that leaves SIMDs
-// without a wave (4096 leaves of 24: 4 / 16 lanes 12.8 / 9.6 us; 512 leaves of
-// 2048: 16 / 64 lanes 120 / 38).
-int p2m_lanes(int64_t n, int64_t nleaf) {
-  constexpr int64_t kSimds = 1024;
-  int g = n >= 64 * nleaf ? 16 : (n >= 16 * nleaf ? 4 : (n >= 6 * nleaf ? 2 : 1));
-  if (nleaf * g < 64 * kSimds) g = 16;
-  if (nleaf * g < 64 * kSimds) g = 64;
-  return g;
-}
-
 template <int P>
 struct P2MRun {
   static hipError_t run(fmm_plan_s* Pl, hipStream_t s) {

@@ -3,9 +3,8 @@ ones) and 64 (very few), with empty leaves, leaves below and above a group.
 
 Charges are zero but for some whole leaves and some scattered particles, so the
 oracle's FMM over those alone has the same potential and force there: FP64 to
-1e-12 (rounding), at any number of particles.  The adaptive tree's two group
-sizes (leaf_max below and from 16) meet its own oracle in the tests of that
-tree."""
+1e-12 (rounding), at any number of particles.  Adaptive
+trees take the same rule and meet their own oracle in the tests of that tree."""
 import numpy as np
 import pytest
 
