@@ -61,26 +61,26 @@ __host__ __device__ inline Cd harm(const double* re, const double* im, int nmax,
   return {sg * re[tri(n, -mm)], -sg * im[tri(n, -mm)]};
 }
 
-// Regular harmonics in FP64, table of m >= 0 (runtime degree).
-__host__ __device__ void regular_table(double x, double y, double z, int p, double* re, double* im) {
+// Column m (degrees n = m..p) of the regular harmonics in FP64 (runtime
+// degree); one thread per order m.
+__host__ __device__ void regular_column(double x, double y, double z, int p, int m, double* re, double* im) {
   const double r2 = x * x + y * y + z * z;
-  re[0] = 1.0;
-  im[0] = 0.0;
-  for (int m = 0; m <= p; ++m) {
-    if (m > 0) {
-      const double pr = re[tri(m - 1, m - 1)], pi = im[tri(m - 1, m - 1)];
-      re[tri(m, m)] = -(x * pr - y * pi) / (2.0 * m);
-      im[tri(m, m)] = -(x * pi + y * pr) / (2.0 * m);
-    }
-    if (m + 1 <= p) {
-      re[tri(m + 1, m)] = z * re[tri(m, m)];
-      im[tri(m + 1, m)] = z * im[tri(m, m)];
-    }
-    for (int n = m + 2; n <= p; ++n) {
-      const double d = (double)(n - m) * (double)(n + m);
-      re[tri(n, m)] = ((2.0 * n - 1.0) * z * re[tri(n - 1, m)] - r2 * re[tri(n - 2, m)]) / d;
-      im[tri(n, m)] = ((2.0 * n - 1.0) * z * im[tri(n - 1, m)] - r2 * im[tri(n - 2, m)]) / d;
-    }
+  double dr = 1.0, di = 0.0;  // R_0^0, then R_k^k
+  for (int k = 1; k <= m; ++k) {
+    const double nr = -(x * dr - y * di) / (2.0 * k), ni = -(x * di + y * dr) / (2.0 * k);
+    dr = nr;
+    di = ni;
+  }
+  re[tri(m, m)] = dr;
+  im[tri(m, m)] = di;
+  if (m + 1 <= p) {
+    re[tri(m + 1, m)] = z * dr;
+    im[tri(m + 1, m)] = z * di;
+  }
+  for (int n = m + 2; n <= p; ++n) {
+    const double d = (double)(n - m) * (double)(n + m);
+    re[tri(n, m)] = ((2.0 * n - 1.0) * z * re[tri(n - 1, m)] - r2 * re[tri(n - 2, m)]) / d;
+    im[tri(n, m)] = ((2.0 * n - 1.0) * z * im[tri(n - 1, m)] - r2 * im[tri(n - 2, m)]) / d;
   }
 }
 
@@ -88,35 +88,9 @@ __host__ __device__ void regular_table(double x, double y, double z, int p, doub
 //   I_0^0 = 1/r,  I_m^m = -(2m-1)(x + i y)/r^2 I_{m-1}^{m-1},
 //   I_{m+1}^m = (2m+1) z / r^2 I_m^m,
 //   r^2 I_n^m = (2n-1) z I_{n-1}^m - (n+m-1)(n-m-1) I_{n-2}^m.
-__host__ __device__ void irregular_table(double x, double y, double z, int p, double* re, double* im) {
-  const double r2 = x * x + y * y + z * z;
-  re[0] = 1.0 / sqrt(r2);
-  im[0] = 0.0;
-  for (int m = 0; m <= p; ++m) {
-    if (m > 0) {
-      const double pr = re[tri(m - 1, m - 1)], pi = im[tri(m - 1, m - 1)];
-      const double f = -(2.0 * m - 1.0) / r2;
-      re[tri(m, m)] = f * (x * pr - y * pi);
-      im[tri(m, m)] = f * (x * pi + y * pr);
-    }
-    if (m + 1 <= p) {
-      const double f = (2.0 * m + 1.0) * z / r2;
-      re[tri(m + 1, m)] = f * re[tri(m, m)];
-      im[tri(m + 1, m)] = f * im[tri(m, m)];
-    }
-    for (int n = m + 2; n <= p; ++n) {
-      const double c1 = (2.0 * n - 1.0) * z, c2 = (double)(n + m - 1) * (double)(n - m - 1);
-      re[tri(n, m)] = (c1 * re[tri(n - 1, m)] - c2 * re[tri(n - 2, m)]) / r2;
-      im[tri(n, m)] = (c1 * im[tri(n - 1, m)] - c2 * im[tri(n - 2, m)]) / r2;
-    }
-  }
-}
-
 constexpr int kTabMax = (2 * FMM_P_MAX + 1) * (2 * FMM_P_MAX + 2) / 2;
 
-// Column m (all degrees n = m..p) of the irregular table, by the same
-// recurrences, with the diagonal entry in closed form
-// I_m^m = (-1)^m (2m-1)!! (x + i y)^m / r^{2m+1}; one thread per order m.
+// Column m (all degrees n = m..p) of their table; one thread per order m.
 __host__ __device__ void irregular_column(double x, double y, double z, int p, int m, double* re,
                                  double* im) {
   const double r2 = x * x + y * y + z * z;
@@ -195,10 +169,10 @@ __global__ void k_gen_shift(int p, int kp, int rp, double* __restrict__ m2m,
   const int oct = blockIdx.x & 7;
   const bool is_l2l = (int)(blockIdx.x >> 3) >= kShiftSplit;
   const int part = (blockIdx.x >> 3) % kShiftSplit;
-  if (threadIdx.x == 0) {
+  if ((int)threadIdx.x <= p) {
     double w[3];
     octant_vector(oct, w);
-    regular_table(w[0], w[1], w[2], p, tre, tim);
+    regular_column(w[0], w[1], w[2], p, threadIdx.x, tre, tim);
   }
   __syncthreads();
   const int nc = (p + 1) * (p + 1);
@@ -326,36 +300,60 @@ __global__ void k_gen_m2l_f64(int p, double* __restrict__ scratch) {
   }
 }
 
-// Pass 2: tbl[row][k] = max over operators of |entry| (FP32).
-__global__ void k_f16_table(int rpkp, const double* __restrict__ scratch, float* __restrict__ tbl) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= rpkp) return;
+// Pass 2: tbl[row][k] = max over operators of |entry| (FP32, rounded after the
+// maximum).  64 entries a work-group, the operators dealt to its 16 waves: one
+// thread per entry was a serial chain of 316 loads in 16 waves per 1024
+// entries (p = 6: 27 -> 5 us).
+__global__ __launch_bounds__(1024) void k_f16_table(int rpkp, const double* __restrict__ scratch,
+                                                    float* __restrict__ tbl) {
+  __shared__ double part[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + lane;
   double m = 0.0;
-  for (int op = 0; op < kNumM2LOps; ++op) m = fmax(m, fabs(scratch[(size_t)op * rpkp + e]));
-  tbl[e] = (float)m;
+  if (e < rpkp) {
+#pragma unroll 4
+    for (int op = wave; op < kNumM2LOps; op += 16) m = fmax(m, fabs(scratch[(size_t)op * rpkp + e]));
+  }
+  part[wave][lane] = m;
+  __syncthreads();
+  if (wave == 0 && e < rpkp) {
+    for (int w = 1; w < 16; ++w) m = fmax(m, part[w][lane]);
+    tbl[e] = (float)m;
+  }
 }
 
-// Pass 3 (one work-group): the row and column exponents, as inverse factors
-// rowf_r = 2^-ra_r and colf_k = 2^-cb_k.
-__global__ void k_f16_fit(int rp, int kp, const float* __restrict__ tbl, float* __restrict__ rowf,
-                          float* __restrict__ colf) {
+// Pass 3 (one work-group of 16 waves): the row and column exponents, as inverse
+// factors rowf_r = 2^-ra_r and colf_k = 2^-cb_k.  A wave per row, then a wave
+// per 64 columns and share of the rows; a maximum is the same in any order.
+__global__ __launch_bounds__(1024) void k_f16_fit(int rp, int kp, const float* __restrict__ tbl,
+                                                  float* __restrict__ rowf, float* __restrict__ colf) {
   __shared__ int ra[256];
-  for (int r = threadIdx.x; r < rp; r += blockDim.x) {
+  __shared__ float part[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int r = wave; r < rp; r += 16) {
     float m = 0.f;
-    for (int k = 0; k < kp; ++k) m = fmaxf(m, tbl[r * kp + k]);
+    for (int k = lane; k < kp; k += 64) m = fmaxf(m, tbl[r * kp + k]);
+    for (int w = 32; w >= 1; w >>= 1) m = fmaxf(m, __shfl_xor(m, w));
     int e = 0;
     if (m > 0.f) frexpf(m, &e);  // m = f 2^e, f in [0.5, 1)
-    ra[r] = -e;                  // max of the row times 2^ra in [0.5, 1)
+    if (lane == 0) ra[r] = -e;   // max of the row times 2^ra in [0.5, 1)
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < kp; k += blockDim.x) {
+  for (int k0 = 0; k0 < kp; k0 += 64) {
+    const int k = k0 + lane;
     float m = 0.f;
-    for (int r = 0; r < rp; ++r) m = fmaxf(m, ldexpf(tbl[r * kp + k], ra[r]));
-    int e = 0;
-    if (m > 0.f) frexpf(m, &e);
-    colf[k] = ldexpf(1.f, e);  // cb_k = -e
+    if (k < kp)
+      for (int r = wave; r < rp; r += 16) m = fmaxf(m, ldexpf(tbl[r * kp + k], ra[r]));
+    part[wave][lane] = m;
+    __syncthreads();
+    if (wave == 0 && k < kp) {
+      for (int w = 1; w < 16; ++w) m = fmaxf(m, part[w][lane]);
+      int e = 0;
+      if (m > 0.f) frexpf(m, &e);
+      colf[k] = ldexpf(1.f, e);  // cb_k = -e
+    }
+    __syncthreads();
   }
-  __syncthreads();
   // every scaled entry is now below 1: shift all rows by 2^14
   for (int r = threadIdx.x; r < rp; r += blockDim.x) rowf[r] = ldexpf(1.f, -(ra[r] + 14));
 }
@@ -440,8 +438,8 @@ hipError_t launch_operators(fmm_plan_s* P, hipStream_t s) {
     float* rowf = wsp<float>(P, lay.f16_rowf);
     float* colf = wsp<float>(P, lay.f16_colf);
     k_gen_m2l_f64<<<kNumM2LOps * kGenSplit, kBlock, 0, s>>>(P->p, scratch);
-    k_f16_table<<<grid_for(rpp * kp, kBlock), kBlock, 0, s>>>(rpp * kp, scratch, tbl);
-    k_f16_fit<<<1, kBlock, 0, s>>>(rpp, kp, tbl, rowf, colf);
+    k_f16_table<<<grid_for(rpp * kp, 64), 1024, 0, s>>>(rpp * kp, scratch, tbl);
+    k_f16_fit<<<1, 1024, 0, s>>>(rpp, kp, tbl, rowf, colf);
     const int64_t items = (int64_t)kNumM2LOps * rpp * m2lb_ksteps(nc) * 4;
     k_f16_split_ops<<<grid_for(items, kBlock), kBlock, 0, s>>>(P->p, P->adaptive, m2l_f16_wide(P->p),
                                                                wide_ops(nc), items, scratch, rowf,
