@@ -27,7 +27,8 @@
 //    chip idle): the waves of a work-group share 16 targets of one
 //    class and split the items (wave w takes w, w + W, ...), operators are read
 //    from L2 by each wave, no barriers; the waves' sums are added pairwise
-//    through LDS in a fixed order.
+//    through LDS in a fixed order.  With very few targets two work-groups share
+//    them (small_parts).
 // Sources outside the domain (or absent) read row 0, which is zero.
 //
 // Bound (FP64, 2^20 charges, depth 6, p = 8): the matrix cores and the vector
@@ -35,8 +36,8 @@
 // 128 padded rows of 81 real) are 3.7 ms and the signed sums 1.2 ms of the
 // block form's 5.9 ms; the kernel with a product per offset took 13.2 ms
 // (depth 5: 2.70 -> 1.20 ms; 2 x 10^5 charges, depth 5, p = 12: 17.5 -> 4.2
-// ms; depth 4, small form: 1.31 -> 0.34 ms; clusters, 3 x 10^5 sites, p = 10:
-// 6.4 -> 2.1 ms).  Operators through LDS with a barrier per step: 9.1 ms (the
+// ms; depth 4, small form: 1.31 -> 0.32 ms; clusters, 3 x 10^5 sites, p = 10:
+// 3.2 -> 1.6 ms).  Operators through LDS with a barrier per step: 9.1 ms (the
 // waves of a SIMD wait together); operators from L2 without a register set
 // ahead: 7.9 ms.
 // FP32: chains of a few items are added to the total with Kahan compensation
@@ -233,6 +234,31 @@ struct Core {
       }
     }
   }
+  // The same with the zero axes known at run time only.  The sources absent on
+  // them are zero, so both partners of a pair hold the one vector.
+  __device__ __forceinline__ void chunk_any(uint32_t zeros, int c, const vec_t* xv, const vec_t* av) {
+    constexpr uint32_t kOdd[3] = {0xAAu, 0xCCu, 0xF0u};  // classes odd under each axis
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      if (NT < V && v >= NT && c == NCH - 1) return;  // the shorter last chunk
+      const int ks = c * V + v;
+      T w[NCLS], s[NAX];
+#pragma unroll
+      for (int x = 0; x < NAX; ++x) s[x] = M::unit((uint32_t)((kb[x] >> ks) & 1u) << 31);
+#pragma unroll
+      for (int e = 0; e < NCLS; ++e) w[e] = xv[e][v];
+      butterfly<0, T>(w, s);
+      uint32_t meets = 0xFFu;  // classes that share a column of the k step
+#pragma unroll
+      for (int x = 0; x < NAX; ++x)
+        if (zeros & (1u << x))
+          meets &= ((bits_t)S::TAB.has[x][0] >> ks & 1u ? ~kOdd[x] : 0u) |
+                   ((bits_t)S::TAB.has[x][1] >> ks & 1u ? kOdd[x] : 0u);
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        if (meets >> S::TAB.bcls[b] & 1u) acc[b] = M::step(av[b][v], w[S::TAB.bcls[b]], acc[b]);
+    }
+  }
   // FP32: the running chain joins the compensated total
   __device__ __forceinline__ void flush() {
     if constexpr (M::kChain) {
@@ -264,13 +290,16 @@ struct Core {
     }
     return wave == 0;
   }
-  __device__ __forceinline__ void store(int kg, T* o) const {
+  __device__ __forceinline__ void store(int kg, T* o, bool add = false) const {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int rc = kTab<P>.rcoef[16 * b + M::row(kg, i)];
-        if (rc >= 0) o[rc] = M::kChain ? sum[b < NBC ? b : 0][i] : acc[b][i];
+        if (rc < 0) continue;
+        const T v = M::kChain ? sum[b < NBC ? b : 0][i] : acc[b][i];
+        if (add) unsafeAtomicAdd(o + rc, v);
+        else o[rc] = v;
       }
   }
 };
@@ -508,9 +537,22 @@ struct Target {
   }
 };
 
-// Gather form (see the head of the file); small: the waves share 16 targets.
+// Whether a chunk's zero axes stay a run-time value: one body instead of seven,
+// some 50 registers fewer (FP64: none spilled; with seven, 15 at p = 10, 361 at
+// p = 12).  FP64, ms, seven bodies -> one: 262 144 charges, depth 4, p = 4 / 8 / 10 /
+// 12: 0.138 / 0.331 / 0.495 / 3.61 -> 0.132 / 0.321 / 0.463 / 1.12; adaptive, 10^6,
+// p = 6 / 10: 1.65 / 4.22 -> 1.55 / 3.98.  FP32 has registers to spare up to p = 10,
+// and there the products that a known axis leaves out by class weigh more (10^6,
+// p = 6 / 10: 0.98 / 2.00 against 1.08 / 2.22); p = 12: 0.72 -> 0.67.
 template <int P, typename T>
-__global__ __launch_bounds__(64 * gather_waves(P), gather_waves(P) / 4) void k_m2l_gather(m2l::Args a, bool small, const T* __restrict__ rows,
+constexpr bool any_zeros() {
+  return sizeof(T) == 8 || P >= 11;
+}
+
+// Gather form (see the head of the file).  parts > 0, the small form: the waves
+// of parts work-groups (1 or 2) share 16 targets.
+template <int P, typename T>
+__global__ __launch_bounds__(64 * gather_waves(P), gather_waves(P) / 4) void k_m2l_gather(m2l::Args a, int parts, const T* __restrict__ rows,
                                                             const T* __restrict__ ops, T* __restrict__ out) {
   typedef Core<P, T> C;
   typedef typename C::S S;
@@ -526,9 +568,15 @@ __global__ __launch_bounds__(64 * gather_waves(P), gather_waves(P) / 4) void k_m
 
   // group -> level, parents and (small) class (XCD-aware: each XCD a contiguous
   // range of groups; small: the 8 classes of the same parents consecutive)
+  const bool small = parts > 0;
   const int64_t per_xcd = (a.ngroups + 7) / 8;
-  const int64_t lg = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  int64_t lg = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (lg >= a.ngroups) return;
+  int first = small ? wave : 0;  // item of the wave
+  if (parts == 2) {
+    first += W * (int)(lg & 1);
+    lg >>= 1;
+  }
   int l = 2;
   while (l < a.L && lg >= a.group_off[l + 1]) ++l;
   const int64_t idx = lg - a.group_off[l];
@@ -584,22 +632,25 @@ __global__ __launch_bounds__(64 * gather_waves(P), gather_waves(P) / 4) void k_m
 
   C core;
   core.init(kg);
-  const int step = small ? W : 1;  // item stride of a wave
+  const int step = small ? W * parts : 1;  // item stride of a wave
   int rb = 0;
-  uint32_t code = kItems.v[pi][small ? wave : 0];
+  uint32_t code = kItems.v[pi][first];
   lookup(code);
   bool any = keep_rows(0);
   if (any) load(code, 0, 0);
 #pragma unroll 1
-  for (int it = small ? wave : 0; it < NI; it += step) {
+  for (int it = first; it < NI; it += step) {
     const bool more = it + step < NI;
     const uint32_t ncode = kItems.v[pi][more ? it + step : it];
     if (more) lookup(ncode);
     if (any) {
 #pragma unroll 1
       for (int c = 0; c < NCH; ++c) {
-        with_zeros(zero_axes(code),
-                        [&](auto zc) { core.template chunk<decltype(zc)::value>(c, xv, av, []() {}); });
+        if constexpr (any_zeros<P, T>())
+          core.chunk_any(zero_axes(code), c, xv, av);
+        else
+          with_zeros(zero_axes(code),
+                     [&](auto zc) { core.template chunk<decltype(zc)::value>(c, xv, av, []() {}); });
         if (c + 1 < NCH) load(code, c + 1, rb);
       }
       core.flush();
@@ -611,14 +662,16 @@ __global__ __launch_bounds__(64 * gather_waves(P), gather_waves(P) / 4) void k_m
   }
 
   if (small && !core.add_waves(red, wave, lane, W)) return;
-  if (t.ok) core.store(kg, out + (a.exp_off[l] + t.row) * S::NC);
+  if (t.ok) core.store(kg, out + (a.exp_off[l] + t.row) * S::NC, parts == 2);
 }
 
 // Multipole rows in the order of the columns (m2l_sym.h row_slot), row 0 zero.
-// A work-group copies 64 rows; reads and writes run along the rows.
+// A work-group copies 64 rows; reads and writes run along the rows.  zero: the
+// results of nz values per box, to which two work-groups will add.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_sym_rows(Tab tab, int str, int64_t box0, int64_t nbox,
-                                                     const T* __restrict__ mult, T* __restrict__ rows) {
+                                                     const T* __restrict__ mult, T* __restrict__ rows,
+                                                     T* __restrict__ zero, int nz) {
   __shared__ int16_t src[4 * kMaxKs];  // coefficient held by each slot
   const int ks = str / 4, v = 16 / (int)sizeof(T);
   for (int r = threadIdx.x; r < str; r += kBlock) src[row_slot(r, ks, v)] = tab.kcoef[r];
@@ -626,7 +679,9 @@ __global__ __launch_bounds__(kBlock) void k_sym_rows(Tab tab, int str, int64_t b
   if (blockIdx.x == 0)
     for (int e = threadIdx.x; e < str; e += kBlock) rows[e] = T(0);
   const int64_t b0 = box0 + (int64_t)blockIdx.x * 64;
-  const int64_t n = (b0 + 64 < nbox ? 64 : nbox - b0) * str;
+  const int64_t nb = b0 + 64 < nbox ? 64 : nbox - b0, n = nb * str;
+  if (zero)
+    for (int64_t e = threadIdx.x; e < nb * nz; e += kBlock) zero[b0 * nz + e] = T(0);
   for (int64_t e = threadIdx.x; e < n; e += kBlock) {
     const int64_t b = b0 + e / str;
     const int c = src[e % str];
@@ -637,6 +692,19 @@ __global__ __launch_bounds__(kBlock) void k_sym_rows(Tab tab, int str, int64_t b
 // Fewest work-groups of the wide forms: with fewer the small form is used, its
 // 8 x more work-groups then fill the chip better.
 constexpr int64_t kWideGroups = 200;
+
+// Work-groups that share 16 targets in the small form, with the work-groups
+// (of one each) that there are.  Two, each walking half of the 56 items (4
+// instead of 7 a wave) and adding to zeroed results (two terms: the order does
+// not matter), where that takes fewer rounds of the 256 CUs, which hold one
+// work-group each (40 work-groups, 4096 charges, depth 3, p = 4 / 8 / 12: 79 / 201 /
+// 664 -> 49 / 121 / 388 us; 296, depth 4, p = 4 / 8: 146 / 350 -> 132 / 320; some 400,
+// p = 8: 358 -> 423, so one).  FP32 stays at one: two rounded terms would be less
+// exact than the compensated total.
+inline int small_parts(int64_t groups, bool fp64) {
+  auto rounds = [](int64_t g) { return (g + 255) / 256; };
+  return fp64 && groups < 512 && 4 * rounds(2 * groups) < 7 * rounds(groups) ? 2 : 1;
+}
 
 template <int P, typename T>
 hipError_t run(fmm_plan_s* Pl, hipStream_t s) {
@@ -649,25 +717,26 @@ hipError_t run(fmm_plan_s* Pl, hipStream_t s) {
   T* out = wsp<T>(Pl, lay.m2l_out);
   const int64_t box0 = exp_box0(Pl), nbox = exp_nbox(Pl);
   if (nbox <= box0) return hipSuccess;
+  // group_off, ngroups: 8 classes x groups of 16 parents
+  m2l::Args a = m2l::make_args(Pl, 16);
+  const bool wide = a.ngroups >= 8 * kWideGroups;
+  const int parts = wide ? 0 : small_parts(a.ngroups, sizeof(T) == 8);
   prof_begin(Pl, FMM_PHASE_M2L, s);
   k_sym_rows<T><<<grid_for(nbox - box0, 64), kBlock, 0, s>>>(Shape<P, T>::TAB, Shape<P, T>::STR, box0, nbox,
-                                                             mult, rows);
-  // group_off, ngroups: 8 classes x groups of 16 parents
-  m2l::Args small = m2l::make_args(Pl, 16);
-  auto shared_by = [&](int classes) {  // work-groups of that many classes each
-    m2l::Args a = small;
+                                                             mult, rows, parts == 2 ? out : nullptr,
+                                                             Shape<P, T>::NC);
+  auto share = [&](int classes) {  // work-groups of that many classes each
     for (int l = 2; l <= a.L + 1; ++l) a.group_off[l] /= classes;
     a.ngroups /= classes;
-    return a;
   };
-  const bool wide = small.ngroups >= 8 * kWideGroups;
+  constexpr int W = gather_waves(P);
   if (wide && !Pl->adaptive) {
-    const m2l::Args a = shared_by(8);
+    share(8);
     k_m2l_block<P, T><<<m2l::grid_of(a), kSymThreads, 0, s>>>(a, rows, ops, out);
   } else {
-    constexpr int W = gather_waves(P);
-    const m2l::Args a = wide ? shared_by(W) : small;
-    k_m2l_gather<P, T><<<m2l::grid_of(a), 64 * W, 0, s>>>(a, !wide, rows, ops, out);
+    if (wide) share(W);
+    if (parts == 2) a.ngroups *= 2;
+    k_m2l_gather<P, T><<<m2l::grid_of(a), 64 * W, 0, s>>>(a, parts, rows, ops, out);
   }
   prof_end(Pl, s);
   return hipGetLastError();

@@ -48,3 +48,17 @@ def test_gather_form_of_a_large_adaptive_tree(p):
     split = run_gpu(pos, q, 6, p, MIXED, side=0.0, leaf_max=12, m2l_kind=B.FMM_M2L_BF16X3)
     check(split, ref, 1e-5, 1e-5, 1e-6)
     check(run_gpu(pos, q, 6, p, MIXED, side=0.0, leaf_max=12, m2l_kind=B.FMM_M2L_F32), ref, 1e-5, 1e-5, 1e-6)
+
+
+@pytest.mark.parametrize("depth,leaf_max,n,p", [(2, 0, 300, 12), (4, 0, 3001, 7), (4, 0, 3001, 11), (5, 2, 6001, 4),
+                                                (4, 2, 2500, 9), (5, 2, 6001, 12)])
+def test_small_form_with_one_and_two_work_groups_per_target(depth, leaf_max, n, p):
+    # 8 and 296 work-groups (two share 16 targets) and, on adaptive trees, about
+    # 250 and 700 (one); two runs are the same to the bit in both
+    pos, q = W.uniform_gauss(n, 40 + p)
+    a = run_gpu(pos, q, depth, p, FP64, leaf_max=leaf_max)
+    b = run_gpu(pos, q, depth, p, FP64, leaf_max=leaf_max)
+    for x, y in zip(a[:2], b[:2]):
+        assert (x == y).all()
+    ref = oracle.fmm_adaptive(pos, q, leaf_max, depth, p, side=1.0) if leaf_max else oracle.fmm(pos, q, depth, p)
+    check(a, ref, 1e-12, 1e-12, 1e-12)
