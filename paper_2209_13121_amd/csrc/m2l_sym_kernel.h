@@ -697,8 +697,8 @@ constexpr int64_t kWideGroups = 200;
 // (of one each) that there are.  Two, each walking half of the 56 items (4
 // instead of 7 a wave) and adding to zeroed results (two terms: the order does
 // not matter), where that takes fewer rounds of the 256 CUs, which hold one
-// work-group each (40 work-groups, 4096 charges, depth 3, p = 4 / 8 / 12: 79 / 201 /
-// 664 -> 49 / 121 / 388 us; 296, depth 4, p = 4 / 8: 146 / 350 -> 132 / 320; some 400,
+// work-group each (40 work-groups, 4096 charges, depth 3, p = 4 / 8: 79 / 201 ->
+// 49 / 121 us; 296, depth 4, p = 4 / 8: 146 / 350 -> 132 / 320; some 400,
 // p = 8: 358 -> 423, so one).  FP32 stays at one: two rounded terms would be less
 // exact than the compensated total.
 inline int small_parts(int64_t groups, bool fp64) {

@@ -143,7 +143,7 @@ __global__ void k_keys(const double* __restrict__ pos, int64_t n, int L, int che
 //  1. k_keys_hist: keys as k_keys, and each work-group's count of every coarse
 //     value (LDS atomics) at hist[c * nblk + block];
 //  2. an exclusive scan of hist (coarse value major): the first position of
-//     each (coarse value, work-group) pair;
+//     each (coarse value, work-group) pair (few work-groups: in step 3);
 //  3. k_coarse_scatter: each particle to its pair's range (LDS atomics give
 //     positions within the work-group), key and index;
 //  4. k_fine: one work-group per coarse value counts its fine digits in LDS,
@@ -185,12 +185,45 @@ __global__ __launch_bounds__(kBlock) void k_keys_hist(const double* __restrict__
   for (int c = threadIdx.x; c < kSortCoarse; c += kBlock) hist[(int64_t)c * nblk + blockIdx.x] = h[c];
 }
 
+// coarse (with few work-groups, kFoldBlocks): off holds the counts themselves;
+// every work-group sums and scans them for its own offsets, and the first
+// leaves the coarse values' starts in coarse[] for k_fine.
 __global__ __launch_bounds__(kBlock) void k_coarse_scatter(const uint32_t* __restrict__ keys, int64_t n, int L,
                                                            const uint32_t* __restrict__ off, int64_t nblk,
+                                                           uint32_t* __restrict__ coarse,
                                                            uint32_t* __restrict__ key_tmp,
                                                            int32_t* __restrict__ idx_tmp) {
   __shared__ uint32_t base[kSortCoarse];
-  for (int c = threadIdx.x; c < kSortCoarse; c += kBlock) base[c] = off[(int64_t)c * nblk + blockIdx.x];
+  if (coarse) {
+    static_assert(kSortCoarse == 2 * kBlock, "two coarse values a thread");
+    __shared__ uint32_t ssum[kBlock];
+    const uint32_t* h = off + 2 * (int64_t)threadIdx.x * nblk;  // counts of the thread's two values
+    uint32_t tot[2] = {0u, 0u}, mine[2] = {0u, 0u};
+    for (int64_t b = 0; b < nblk; ++b)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t v = h[k * nblk + b];
+        tot[k] += v;
+        mine[k] += b < blockIdx.x ? v : 0u;
+      }
+    ssum[threadIdx.x] = tot[0] + tot[1];
+    __syncthreads();
+    for (int w = 1; w < kBlock; w <<= 1) {
+      const uint32_t add = (int)threadIdx.x >= w ? ssum[threadIdx.x - w] : 0u;
+      __syncthreads();
+      ssum[threadIdx.x] += add;
+      __syncthreads();
+    }
+    const uint32_t first = ssum[threadIdx.x] - tot[0] - tot[1];
+    base[2 * threadIdx.x] = first + mine[0];
+    base[2 * threadIdx.x + 1] = first + tot[0] + mine[1];
+    if (blockIdx.x == 0) {
+      coarse[2 * threadIdx.x] = first;
+      coarse[2 * threadIdx.x + 1] = first + tot[0];
+    }
+  } else {
+    for (int c = threadIdx.x; c < kSortCoarse; c += kBlock) base[c] = off[(int64_t)c * nblk + blockIdx.x];
+  }
   __syncthreads();
   const int sh = 3 * L - 9;
   constexpr int R = kSortChunk / kBlock;
@@ -214,7 +247,8 @@ __global__ __launch_bounds__(kBlock) void k_coarse_scatter(const uint32_t* __res
 // the particles (a dense system of a batch), and its two passes over them
 // are the longest work-group of the launch.
 constexpr int kFineThreads = 1024;
-__global__ __launch_bounds__(kFineThreads) void k_fine(int64_t n, int L, const uint32_t* __restrict__ off, int64_t nblk,
+// off[c * stride]: first position of coarse value c.
+__global__ __launch_bounds__(kFineThreads) void k_fine(int64_t n, int L, const uint32_t* __restrict__ off, int64_t stride,
                                                  const uint32_t* __restrict__ key_tmp,
                                                  const int32_t* __restrict__ idx_tmp,
                                                  uint32_t* __restrict__ count, uint32_t* __restrict__ start,
@@ -224,7 +258,7 @@ __global__ __launch_bounds__(kFineThreads) void k_fine(int64_t n, int L, const u
   const int tid = threadIdx.x;
   const int64_t c = blockIdx.x;
   const int fb = 1 << (3 * L - 9);
-  const uint32_t b0 = off[c * nblk], b1 = off[(c + 1) * nblk];
+  const uint32_t b0 = off[c * stride], b1 = c + 1 < kSortCoarse ? off[(c + 1) * stride] : (uint32_t)n;
   for (int f = tid; f < fb; f += kFineThreads) cnt[f] = 0;
   __syncthreads();
   for (uint32_t j = b0 + tid; j < b1; j += kFineThreads) atomicAdd(&cnt[key_tmp[j] & (uint32_t)(fb - 1)], 1u);
@@ -320,8 +354,30 @@ __global__ void k_scatter(const uint32_t* __restrict__ keys, int64_t n,
   perm_tmp[start[k] + atomicAdd(&fill[k], 1u)] = (int32_t)i;
 }
 
-// Inside each leaf, order particles by user index (rank = number of smaller
-// indices in the same leaf).
+// Inside each leaf, order particles by user index: rank = number of smaller
+// indices among perm[b .. e).  Four at a time from the aligned quad of b on (perm
+// is aligned and padded to quads); one by one the loads bound it (2^20 charges,
+// depth 4, 256 per leaf: k_rank_gather 110 -> 72 us, of which the gather is 40).
+__device__ __forceinline__ uint32_t rank_in_leaf(const int32_t* __restrict__ perm, uint32_t b, uint32_t e,
+                                                 int32_t me) {
+  uint32_t rank = 0;
+  auto part = [&](uint32_t t) {  // a quad that may reach outside
+    const int4 v = *reinterpret_cast<const int4*>(perm + t);
+    rank += (t >= b && v.x < me) ? 1u : 0u;
+    rank += (t + 1 >= b && t + 1 < e && v.y < me) ? 1u : 0u;
+    rank += (t + 2 >= b && t + 2 < e && v.z < me) ? 1u : 0u;
+    rank += (t + 3 >= b && t + 3 < e && v.w < me) ? 1u : 0u;
+  };
+  uint32_t t = b & ~3u;
+  part(t);
+  for (t += 4; t + 4 <= e; t += 4) {
+    const int4 v = *reinterpret_cast<const int4*>(perm + t);
+    rank += (v.x < me ? 1u : 0u) + (v.y < me ? 1u : 0u) + (v.z < me ? 1u : 0u) + (v.w < me ? 1u : 0u);
+  }
+  if (t < e) part(t);
+  return rank;
+}
+
 __global__ void k_rank(const int32_t* __restrict__ perm_tmp, const uint32_t* __restrict__ keys,
                        int64_t n, const uint32_t* __restrict__ start,
                        const uint32_t* __restrict__ count, int32_t* __restrict__ perm) {
@@ -330,9 +386,7 @@ __global__ void k_rank(const int32_t* __restrict__ perm_tmp, const uint32_t* __r
   const int32_t me = perm_tmp[s];
   const uint32_t leaf = keys[me];
   const uint32_t b = start[leaf], c = count[leaf];
-  uint32_t rank = 0;
-  for (uint32_t t = b; t < b + c; ++t) rank += (perm_tmp[t] < me) ? 1u : 0u;
-  perm[b + rank] = me;
+  perm[b + rank_in_leaf(perm_tmp, b, b + c, me)] = me;
 }
 
 __global__ void k_luts(int L, int64_t nbox, Layout lay,
@@ -391,9 +445,7 @@ __global__ void k_rank_gather(const int32_t* __restrict__ perm_tmp, const uint32
   const int32_t me = perm_tmp[s];
   const uint32_t leaf = keys[me];
   const uint32_t b = start[leaf], c = count[leaf];
-  uint32_t rank = 0;
-  for (uint32_t t = b; t < b + c; ++t) rank += (perm_tmp[t] < me) ? 1u : 0u;
-  const int64_t d = (int64_t)b + rank;
+  const int64_t d = (int64_t)b + rank_in_leaf(perm_tmp, b, b + c, me);
   perm[d] = me;
   sorted_leaf[d] = leaf;
   write_record<T>(pos, me, leaf, d, L, dp, s2c_leaf, src, src64);
@@ -502,7 +554,9 @@ hipError_t launch_tree(fmm_plan_s* P, const double* d_pos, hipStream_t s) {
     const int64_t words = (int64_t)(zero_row_bytes(P->p, P->m2l_np) / 4);
     k_fill_u32<<<grid_for(words, kBlock), kBlock, 0, s>>>(wsp<uint32_t>(P, lay.zero_row), words, 0u);
   }
-  k_luts<<<grid_for(lay.nbox, kBlock), kBlock, 0, s>>>(L, lay.nbox, lay, c2s, s2c);
+  // the coordinate maps depend on the depth alone: a re-plan that keeps the
+  // operators has them too
+  if (!P->ops_ready) k_luts<<<grid_for(lay.nbox, kBlock), kBlock, 0, s>>>(L, lay.nbox, lay, c2s, s2c);
   int32_t* perm_tmp = wsp<int32_t>(P, lay.perm_tmp);
   int32_t* perm = wsp<int32_t>(P, lay.perm);
   if (sort_two_level(L)) {
@@ -512,12 +566,19 @@ hipError_t launch_tree(fmm_plan_s* P, const double* d_pos, hipStream_t s) {
     uint32_t* hist = wsp<uint32_t>(P, lay.sort_hist);
     uint32_t* key_tmp = wsp<uint32_t>(P, lay.sorted_leaf);
     k_keys_hist<<<(unsigned)nblk, kBlock, 0, s>>>(d_pos, n, L, given ? 1 : 0, dp, keys, flags, hist, nblk);
-    const int64_t nh = sort_hist_elems(n);  // the last element (0) becomes the total
-    k_fill_u32<<<1, 1, 0, s>>>(hist + nh - 1, 1, 0u);
-    hipError_t e = scan_exclusive(hist, nh, nh, hist, wsp<uint32_t>(P, lay.scan_tmp), s);
-    if (e != hipSuccess) return e;
-    k_coarse_scatter<<<(unsigned)nblk, kBlock, 0, s>>>(keys, n, L, hist, nblk, key_tmp, perm);
-    k_fine<<<kSortCoarse, kFineThreads, 0, s>>>(n, L, hist, nblk, key_tmp, perm, count, start, perm_tmp);
+    // few work-groups (n <= 32768): three scan launches cost more than the
+    // counts read by every one of them (4096 charges: 12 -> 4 us)
+    constexpr int64_t kFoldBlocks = 32;
+    const bool fold = nblk <= kFoldBlocks;
+    if (!fold) {
+      const int64_t nh = kSortCoarse * nblk;
+      hipError_t e = scan_exclusive(hist, nh, nh, hist, wsp<uint32_t>(P, lay.scan_tmp), s);
+      if (e != hipSuccess) return e;
+    }
+    uint32_t* coarse = fold ? fill : nullptr;  // the one-level sort's array, of 8^L >= 512
+    k_coarse_scatter<<<(unsigned)nblk, kBlock, 0, s>>>(keys, n, L, hist, nblk, coarse, key_tmp, perm);
+    k_fine<<<kSortCoarse, kFineThreads, 0, s>>>(n, L, fold ? coarse : hist, fold ? 1 : nblk, key_tmp, perm, count,
+                                                start, perm_tmp);
   } else {
     k_fill_u32<<<grid_for(lay.nleaf, kBlock), kBlock, 0, s>>>(count, lay.nleaf, 0u);
     k_fill_u32<<<grid_for(lay.nleaf, kBlock), kBlock, 0, s>>>(fill, lay.nleaf, 0u);
