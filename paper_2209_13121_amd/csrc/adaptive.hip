@@ -388,39 +388,10 @@ __global__ void k_zero_stats(unsigned long long* st) {
 //   I_0^0 = 1/r,  I_m^m = -(2m-1)(x + i y)/r^2 I_{m-1}^{m-1},
 //   I_{m+1}^m = (2m+1) z/r^2 I_m^m,
 //   r^2 I_n^m = (2n-1) z I_{n-1}^m - (n+m-1)(n-m-1) I_{n-2}^m;
-// outputs indexed by tri(n, m).
-template <int Q, typename T>
-__device__ __forceinline__ void irregular_harmonics(T x, T y, T z, T* re, T* im) {
-  const T r2 = x * x + y * y + z * z;
-  const T ir2 = T(1) / r2;
-  re[0] = T(1) / sqrt(r2);
-  im[0] = T(0);
-#pragma unroll
-  for (int m = 0; m <= Q; ++m) {
-    if (m > 0) {
-      const T s = T(-(2.0 * m - 1.0)) * ir2;
-      const T pr = re[tri(m - 1, m - 1)], pi = im[tri(m - 1, m - 1)];
-      re[tri(m, m)] = s * (x * pr - y * pi);
-      im[tri(m, m)] = s * (x * pi + y * pr);
-    }
-    if (m + 1 <= Q) {
-      const T s = T(2.0 * m + 1.0) * z * ir2;
-      re[tri(m + 1, m)] = s * re[tri(m, m)];
-      im[tri(m + 1, m)] = s * im[tri(m, m)];
-    }
-#pragma unroll
-    for (int n = m + 2; n <= Q; ++n) {
-      const T a = T(2.0 * n - 1.0) * z, b = T((double)(n + m - 1) * (double)(n - m - 1));
-      re[tri(n, m)] = (a * re[tri(n - 1, m)] - b * re[tri(n - 2, m)]) * ir2;
-      im[tri(n, m)] = (a * im[tri(n - 1, m)] - b * im[tri(n - 2, m)]) * ir2;
-    }
-  }
-}
-
-// The same values, in the same order and arithmetic, handed to f(n, m, re, im)
-// as the recurrence produces them, so that only its last two terms stay live.
+// handed to f(n, m, re, im) as the recurrence produces them, so that only its
+// last two terms stay live.
 template <int Q, typename T, typename F>
-__device__ __forceinline__ void irregular_harmonics_each(T x, T y, T z, F&& f) {
+__device__ __forceinline__ void irregular_harmonics(T x, T y, T z, F&& f) {
   const T r2 = x * x + y * y + z * z;
   const T ir2 = T(1) / r2;
   T dre = T(1) / sqrt(r2), dim = T(0);  // I_m^m
@@ -545,7 +516,7 @@ __global__ __launch_bounds__(64) void k_p2l(ATree t, const uint32_t* __restrict_
       const T oz = (T)(((double)cc[2] + 0.5) * sc - ((double)bc[2] + 0.5));
       const T sg = (T)sc;
       const Rec<T> r = src[t.range[2 * c] + (j - before)];
-      irregular_harmonics_each<P, T>(
+      irregular_harmonics<P, T>(
           ox + sg * r.x, oy + sg * r.y, oz + sg * r.z, [&](int nn, int m, T re, T im) {
             if (m < M0 || m >= M1) return;
             acc[orders_pos(M0, M1, nn, m, false)] += r.q * re;
@@ -578,94 +549,137 @@ __global__ __launch_bounds__(64) void k_p2l(ATree t, const uint32_t* __restrict_
 
 // M2P over the W list of a leaf, added to the far field L2P wrote: one
 // work-group of kM2pWaves waves per leaf of the compact list wbox (the leaves
-// whose W list is not empty), a lane per particle (64 at a time).  Wave v
-// takes the W entries v, v + kM2pWaves, ... in list order, so all lanes of a
-// wave read the same multipole at once; the waves' sums are added in wave
-// order through LDS.
+// whose W list is not empty).  A wave holds E = 4, 2 or 1 entries at a time, a
+// group of 16, 32 or 64 lanes each with a lane per particle (leaves hold some 10
+// particles, W lists some 10 entries), their multipoles in LDS.  Each lane's sums
+// are added over the groups of its wave, then over the waves, in a fixed order.
+// The harmonics I_n^m to degree p + 1 come one at a time; each meets the up to
+// four coefficients whose potential or derivative it belongs to, so none is kept.
+// Bound by the vector unit and the latency of the short lists.  With one entry a
+// wave (lanes past the leaf's particles idle) and the table of harmonics in
+// registers (one wave a SIMD in FP64) it took 936 us, now 432 (3 10^5 in clusters,
+// p = 10, FP64); 3 10^6, p = 10, mixed 1170 -> 759; 256 systems, p = 6: 275 -> 223.
+// With z = I_n^m, N = n - 1 (d/dz I_N^m = -I_n^m, d/dx, d/dy from I_n^{m+-1}):
+//   phi       += w Re(M_n^m z)
+//   d/dx      += Re(M_N^{m-1} z) - Re(M_N^{m+1} z)
+//   d/dy      += Im(M_N^{m-1} z) + Im(M_N^{m+1} z)
+//   d/dz      -= w Re(M_N^m z)            w = 1 for m = 0, else 2
 constexpr int kM2pWaves = 4;
 template <int P, typename T>
-__global__ __launch_bounds__(64 * kM2pWaves, sizeof(T) == 4 && P <= 10 ? 2 : 1) void k_m2p(ATree t, const uint32_t* __restrict__ wbox,
-                                            const Rec<T>* __restrict__ src, int64_t n,
-                                            const DevParams* __restrict__ dp,
-                                            const T* __restrict__ mult,
-                                            const uint32_t* __restrict__ woff,
-                                            const uint32_t* __restrict__ widx,
-                                            double* __restrict__ far_phi,
-                                            double* __restrict__ far_grad) {
+__global__ __launch_bounds__(64 * kM2pWaves, 2) void k_m2p(ATree t, const uint32_t* __restrict__ wbox,
+                                                           const Rec<T>* __restrict__ src, int64_t n,
+                                                           const DevParams* __restrict__ dp,
+                                                           const T* __restrict__ mult,
+                                                           const uint32_t* __restrict__ woff,
+                                                           const uint32_t* __restrict__ widx,
+                                                           double* __restrict__ far_phi,
+                                                           double* __restrict__ far_grad) {
   constexpr int MS = mstride_of((P + 1) * (P + 1));
-  constexpr int NT1 = (P + 2) * (P + 3) / 2;
+  constexpr int R = (4 * MS + 63) / 64;
   __shared__ double red[kM2pWaves][4][64];
-  // the wave index, uniform over the wave (so the multipole reads stay scalar)
+  __shared__ T mults[kM2pWaves][4 * MS];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t leaf = wbox[blockIdx.x];  // a leaf whose W list is not empty
   const uint32_t k0 = woff[leaf], k1 = woff[leaf + 1];
   const uint32_t s0 = t.range[2 * leaf], cnt = t.range[2 * leaf + 1];
   const int l = t.level[leaf];
-  for (uint32_t base = 0; base < cnt; base += 64) {
-    const uint32_t j = base + lane;
+  int lc[3];
+  unpack_coord(t.coord[leaf], lc[0], lc[1], lc[2]);
+  const uint32_t G = cnt <= 16 ? 16 : (cnt <= 32 ? 32 : 64), E = 64 / G;
+  const uint32_t e = lane / G;
+  T* mw = mults[wv];
+  const T* Mw = mw + e * MS;
+  T nx[R];
+  uint32_t w = 0;
+  // the wave's entries k .. k + E - 1 on their way: the group's box, a share of
+  // their multipoles (zero past the end of the list)
+  auto fetch = [&](uint32_t k) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const uint32_t x = lane + 64 * i, ent = x / MS;
+      nx[i] = ent < E && k + ent < k1 ? mult[(int64_t)widx[k + ent] * MS + x % MS] : T(0);
+    }
+    w = widx[k + e < k1 ? k + e : k1 - 1];
+  };
+  for (uint32_t base = 0; base < cnt; base += G) {
+    const uint32_t j = base + lane % G;
     const bool active = j < cnt;
     const int64_t s = s0 + (active ? j : 0);
     const Rec<T> r = src[s];
     double phi = 0.0, g[3] = {0.0, 0.0, 0.0};
-    int lc[3];
-    unpack_coord(t.coord[leaf], lc[0], lc[1], lc[2]);
-    for (uint32_t k = k0 + wv; k < k1; k += kM2pWaves) {
-      const uint32_t w = widx[k];
+    uint32_t k = k0 + wv * E;
+    if (k < k1) fetch(k);
+    for (; k < k1; k += kM2pWaves * E) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const uint32_t x = lane + 64 * i;
+        if (x < 4 * MS) mw[x] = nx[i];
+      }
+      __builtin_amdgcn_wave_barrier();
       const int lw = t.level[w];  // > l
       int wc[3];
       unpack_coord(t.coord[w], wc[0], wc[1], wc[2]);
+      if (k + kM2pWaves * E < k1) fetch(k + kM2pWaves * E);
       // the particle's offset from w's centre in w's units, from the leaf-unit
       // offset u: (leaf centre - w centre)/h_w + u h_leaf/h_w, the centre part exact
       const double sc = (double)(1 << (lw - l));
       const T vx = (T)(((double)lc[0] + 0.5) * sc - ((double)wc[0] + 0.5)) + (T)sc * r.x;
       const T vy = (T)(((double)lc[1] + 0.5) * sc - ((double)wc[1] + 0.5)) + (T)sc * r.y;
       const T vz = (T)(((double)lc[2] + 0.5) * sc - ((double)wc[2] + 0.5)) + (T)sc * r.z;
-      T re[NT1], im[NT1];
-      irregular_harmonics<P + 1, T>(vx, vy, vz, re, im);
-      const T* Mw = mult + (int64_t)w * MS;
-      T f = T(0), gx = T(0), gy = T(0), gz = T(0);
-      // I_{n+1}^{m-1} at m = 0 is I_{n+1}^{-1} = -conj(I_{n+1}^1)
-      auto ir = [&](int nn, int m) { return m >= 0 ? re[tri(nn, m)] : -re[tri(nn, 1)]; };
-      auto ii = [&](int nn, int m) { return m >= 0 ? im[tri(nn, m)] : im[tri(nn, 1)]; };
-  #pragma unroll
-      for (int nn = 0; nn <= P; ++nn) {
-  #pragma unroll
-        for (int m = 0; m <= nn; ++m) {
+      T f0 = T(0), f1 = T(0), gx = T(0), gy = T(0), gz0 = T(0), gz1 = T(0);
+      irregular_harmonics<P + 1, T>(vx, vy, vz, [&](int nn, int m, T re, T im) {
+        if (nn <= P) {
           const T mr = Mw[cidx_re(nn, m)];
-          const T mi = m ? Mw[cidx_im(nn, m)] : T(0);
-          const T wgt = m ? T(2) : T(1);  // the negative orders are the conjugates
-          // Re(M I_n^m)
-          f += wgt * (mr * re[tri(nn, m)] - mi * im[tri(nn, m)]);
-          // d/dx: M (I_{n+1}^{m+1} - I_{n+1}^{m-1}) / 2
-          const T dxr = T(0.5) * (re[tri(nn + 1, m + 1)] - ir(nn + 1, m - 1));
-          const T dxi = T(0.5) * (im[tri(nn + 1, m + 1)] - ii(nn + 1, m - 1));
-          gx += wgt * (mr * dxr - mi * dxi);
-          // d/dy: M (-i/2)(I_{n+1}^{m+1} + I_{n+1}^{m-1}); (-i/2)(a + i b) = b/2 - i a/2
-          const T sr = re[tri(nn + 1, m + 1)] + ir(nn + 1, m - 1);
-          const T si = im[tri(nn + 1, m + 1)] + ii(nn + 1, m - 1);
-          gy += wgt * (mr * (T(0.5) * si) - mi * (T(-0.5) * sr));
-          // d/dz: -M I_{n+1}^m
-          gz -= wgt * (mr * re[tri(nn + 1, m)] - mi * im[tri(nn + 1, m)]);
+          if (m == 0) f0 += mr * re;
+          else f1 += mr * re - Mw[cidx_im(nn, m)] * im;
         }
-      }
+        const int N = nn - 1;
+        if (m >= 1) {  // M_N^{m-1}
+          const T mr = Mw[cidx_re(N, m - 1)];
+          gx += mr * re;
+          gy += mr * im;
+          if (m >= 2) {
+            const T mi = Mw[cidx_im(N, m - 1)];
+            gx -= mi * im;
+            gy += mi * re;
+          }
+        }
+        if (m + 1 <= N) {  // M_N^{m+1}
+          const T mr = Mw[cidx_re(N, m + 1)], mi = Mw[cidx_im(N, m + 1)];
+          gx -= mr * re;
+          gy += mi * re;
+          if (m >= 1) {
+            gx += mi * im;
+            gy += mr * im;
+          }
+        }
+        if (N >= m) {  // M_N^m
+          const T mr = Mw[cidx_re(N, m)];
+          if (m == 0) gz0 += mr * re;
+          else gz1 += mr * re - Mw[cidx_im(N, m)] * im;
+        }
+      });
       const double inv_hw = (double)(1 << lw) / dp->side;
-      phi += inv_hw * (double)f;
+      phi += inv_hw * (double)(f0 + T(2) * f1);
       g[0] += inv_hw * inv_hw * (double)gx;
       g[1] += inv_hw * inv_hw * (double)gy;
-      g[2] += inv_hw * inv_hw * (double)gz;
+      g[2] -= inv_hw * inv_hw * (double)(gz0 + T(2) * gz1);
+      __builtin_amdgcn_wave_barrier();
     }
-    red[wv][0][lane] = phi;
-    red[wv][1][lane] = g[0];
-    red[wv][2][lane] = g[1];
-    red[wv][3][lane] = g[2];
+    double v[4] = {phi, g[0], g[1], g[2]};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (G <= 32) v[q] += __shfl_xor(v[q], 32);
+      if (G <= 16) v[q] += __shfl_xor(v[q], 16);
+      red[wv][q][lane] = v[q];
+    }
     __syncthreads();
-    if (wv == 0 && active) {
-      double v[4];
+    if (wv == 0 && e == 0 && active) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         v[q] = red[0][q][lane];
 #pragma unroll
-        for (int w = 1; w < kM2pWaves; ++w) v[q] += red[w][q][lane];
+        for (int u = 1; u < kM2pWaves; ++u) v[q] += red[u][q][lane];
       }
       far_phi[s] += v[0];
       far_grad[s] += v[1];
