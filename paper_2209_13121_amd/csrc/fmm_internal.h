@@ -30,8 +30,6 @@ constexpr int kMaxProfile = 8192;    // recorded launches between profile reads
 
 // Error bits raised by kernels (atomicOr into Plan::d_flags).
 enum : int32_t { kFlagOutOfCube = 1, kFlagNonFinite = 2, kFlagCoincident = 4, kFlagListOverflow = 8 };
-// Word of the flags' array that counts finished blocks of the energy sum.
-constexpr int kEnergyTicket = 3;
 
 // Device-resident parameters of a plan (written by kernels, so that a derived
 // cube never needs a host round trip).

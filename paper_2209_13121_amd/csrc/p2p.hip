@@ -625,24 +625,11 @@ __global__ __launch_bounds__(64, waves_per_simd<T>()) void k_p2p_group(
   }
 }
 
-// Sum of red[0 .. kBlock) into red[0], in a fixed tree order.
-__device__ __forceinline__ void block_sum(double* red) {
-  __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-}
-
 // E = 1/2 sum q_i phi_i: per-block sums of 4 * kBlock consecutive terms in a
-// fixed tree order; the last block to finish sums the block sums, in a fixed
-// order too, whichever it is.  ticket: blocks that have finished, zero before
-// and after.  (A second launch for the last sum cost its 4.5 us: the sums
-// themselves take 1.)
-__global__ __launch_bounds__(kBlock) void k_energy(const double* __restrict__ eterm, int64_t n, double* part,
-                                                   unsigned* ticket, double* __restrict__ e) {
+// fixed tree order, then one block over the block sums (or, of few terms, over
+// the terms).
+__global__ void k_energy_blocks(const double* __restrict__ eterm, int64_t n, double* __restrict__ part) {
   __shared__ double red[kBlock];
-  __shared__ bool last;
   double s = 0.0;
   const int64_t base = (int64_t)blockIdx.x * 4 * kBlock;
   for (int r = 0; r < 4; ++r) {
@@ -650,23 +637,25 @@ __global__ __launch_bounds__(kBlock) void k_energy(const double* __restrict__ et
     if (i < n) s += eterm[i];
   }
   red[threadIdx.x] = s;
-  block_sum(red);
-  if (threadIdx.x == 0) {
-    part[blockIdx.x] = red[0];
-    __threadfence();  // the sum is seen by whoever sees the ticket
-    last = atomicAdd(ticket, 1u) == gridDim.x - 1;
-  }
   __syncthreads();
-  if (!last) return;
-  __threadfence();
-  s = 0.0;
-  for (int64_t b = threadIdx.x; b < gridDim.x; b += kBlock) s += part[b];
-  red[threadIdx.x] = s;
-  block_sum(red);
-  if (threadIdx.x == 0) {
-    e[0] = 0.5 * red[0];
-    *ticket = 0u;
+  for (int w = kBlock / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
   }
+  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+}
+
+__global__ void k_energy(const double* __restrict__ part, int64_t nparts, double* __restrict__ e) {
+  __shared__ double red[kBlock];
+  double s = 0.0;
+  for (int64_t b = threadIdx.x; b < nparts; b += kBlock) s += part[b];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = kBlock / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) e[0] = 0.5 * red[0];
 }
 
 }  // namespace
@@ -786,8 +775,15 @@ hipError_t launch_near_and_finish(fmm_plan_s* P, double* d_phi, double* d_force,
     prof_begin(P, FMM_PHASE_ENERGY, s);
     const int64_t nparts = (n + 4 * kBlock - 1) / (4 * kBlock);
     double* part = eterm + n;
-    k_energy<<<(unsigned)nparts, kBlock, 0, s>>>(
-        eterm, n, part, reinterpret_cast<unsigned*>(wsp<int32_t>(P, lay.flags) + kEnergyTicket), d_energy);
+    // few terms: one block sums them alone (4096: 5.5 us against 9.1 for the two
+    // launches; 10 007: 11.2 against 9.2).  A last block that adds the block sums
+    // in one launch was slower: the fences of 1024 blocks took 9 to 27 us.
+    if (n <= 16 * kBlock) {
+      k_energy<<<1, kBlock, 0, s>>>(eterm, n, d_energy);
+    } else {
+      k_energy_blocks<<<(unsigned)nparts, kBlock, 0, s>>>(eterm, n, part);
+      k_energy<<<1, kBlock, 0, s>>>(part, nparts, d_energy);
+    }
     prof_end(P, s);
   }
   return hipGetLastError();

@@ -30,7 +30,6 @@ __global__ void k_set_params(DevParams* dp, int32_t* flags, double lo0, double l
   dp->lo[2] = lo2;
   dp->side = side;
   flags[0] = 0;
-  flags[kEnergyTicket] = 0;
 }
 
 // Derived cube: per-block min / max of each axis over finite coordinates.
@@ -104,7 +103,6 @@ __global__ void k_bbox_final(const double* __restrict__ part, int nparts, DevPar
   }
   dp->side = side > 0.0 ? side : 1.0;
   flags[0] = 0;
-  flags[kEnergyTicket] = 0;
 }
 
 __device__ __forceinline__ int leaf_cell(double x, double lo, double side, int L, bool check_cube,

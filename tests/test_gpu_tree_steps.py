@@ -1,6 +1,6 @@
 """The leaf sort on both sides of its rule for few work-groups (n = 32768), leaves
 of more and fewer particles than a quad that start at every residue, and the
-energy's single launch over one and many blocks.
+energy's sum by one block (n <= 4096) and by many.
 
 Sorted order: a plan's results do not depend on the order of its input, so a
 permuted input gives the permuted output to rounding of the sums (order inside
@@ -16,7 +16,7 @@ from paper_2209_13121_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,depth,leaf_max", [(1, 3, 0), (5, 3, 0), (1023, 3, 0), (1025, 4, 0), (32767, 3, 0),
+@pytest.mark.parametrize("n,depth,leaf_max", [(1, 3, 0), (5, 3, 0), (1023, 3, 0), (1025, 4, 0), (4096, 3, 0), (4097, 4, 0), (32767, 3, 0),
                                               (32768, 4, 0), (32769, 4, 0), (40001, 3, 0), (20000, 5, 24),
                                               (40001, 5, 24)])
 def test_sorted_order_and_energy(n, depth, leaf_max):
