@@ -26,7 +26,7 @@
 //    the MFMAs of chunk q.  All 128 targets share each staged operator.
 //  * B operand (source coefficients): 16-byte vectors from global memory; a
 //    whole offset's vectors are prefetched while the previous offset's MFMAs
-//    run (two register sets used alternately) where the registers allow.
+////    run (two register sets used alternately).
 //    Sources outside the domain read a zero row.  All loads are unconditional
 //    (clamped addresses) so the waits on them are exact.
 //  * FP32: each offset's product is a fresh MFMA chain and the chains are
@@ -69,12 +69,6 @@ struct Mfma<float> {
     comp = (t - sum) - y;
     sum = t;
   }
-  static __device__ __forceinline__ void add1(float& sum, float& comp, float v) {
-    const float y = v - comp;
-    const float t = sum + y;
-    comp = (t - sum) - y;
-    sum = t;
-  }
 };
 template <>
 struct Mfma<double> {
@@ -87,61 +81,32 @@ struct Mfma<double> {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ void add(acc_t& sum, acc_t&, acc_t v) { sum += v; }
-  static __device__ __forceinline__ void add1(double& sum, double&, double v) { sum += v; }
 };
-
-constexpr int kLdsBudget = 140 * 1024;  // two operator buffers (plus the slot halo)
-
 
 // Static shape of the kernel for order P and type T.
 template <int P, typename T>
 struct Shape {
   static constexpr int NC = (P + 1) * (P + 1);
-  static constexpr int RB = (NC + 15) / 16;    // 16-row blocks
-  static constexpr int RP = RB * 16;
-  // NC = 16 RBM + 1 (p = 6, 8): the last row is a per-lane dot product on the
-  // vector ALU instead of a 16-row MFMA block holding one real row.
-  static constexpr bool TAIL = NC % 16 == 1 && NC > 16;
-  static constexpr int RBM = TAIL ? RB - 1 : RB;  // MFMA row blocks
-  static constexpr int ROWS = TAIL ? NC : RP;     // operator rows staged in LDS
+  static_assert(NC <= 16, "one 16-row block");
+  static constexpr int RBM = 1;                // 16-row blocks
+  static constexpr int ROWS = 16;              // operator rows, staged in LDS
   static constexpr int MS = mstride_of(NC);    // multipole row stride
   static constexpr int V = Mfma<T>::V;         // elements per vector
   static constexpr int G = 4 * V;              // k per quad chunk
   static constexpr int NQ = (NC + G - 1) / G;  // quad chunks
   static constexpr int S_LAST = NC - G * (NQ - 1) < V ? NC - G * (NQ - 1) : V;
   static constexpr int KS = m2l_kstride_of(NC, (int)sizeof(T));  // global row stride
-  // quad chunks per staged operator chunk: as many as fit two LDS buffers
-  // LDS row layout of a staged chunk of n quad chunks, in 16-byte vectors.
-  // A 16-byte LDS read serves 32 lanes at a time and is free of bank
-  // conflicts when their vectors are distinct modulo 32.
-  //  * Conflict-free form: [g][quad chunk], the 4 lane groups g GQ vectors
-  //    apart (GQ odd) and rows 4 GQ + 2 apart: 16 rows at a stride of 2 mod 4
-  //    fill the even residues, the odd g offset the odd ones.
-  //  * Compact form, where the first needs more operator chunks: [quad
-  //    chunk][g], rows 4 n + 1 apart (adjacent lane groups share banks).
-  static constexpr int gq_of(int n) { return n | 1; }
-  static constexpr int row_cf(int n) { return 4 * gq_of(n) + 2; }
-  static constexpr int row_compact(int n) { return 4 * n + 1; }
-  static constexpr int fit_cf(int n) {
-    return n <= 1 ? 1 : (2 * ROWS * row_cf(n) * 16 <= kLdsBudget ? n : fit_cf(n - 1));
-  }
-  static constexpr int fit_compact(int n) {
-    return n <= 1 ? 1 : (2 * ROWS * row_compact(n) * 16 <= kLdsBudget ? n : fit_compact(n - 1));
-  }
-  static constexpr bool CF = fit_cf(NQ) == fit_compact(NQ);
-  static constexpr int fit_nqc(int n) { return CF ? fit_cf(n) : fit_compact(n); }
-  static constexpr int NQC = fit_nqc(NQ);
-  static constexpr int NCH = (NQ + NQC - 1) / NQC;  // operator chunks
-  static constexpr int KC = G * NQC;                // k per operator chunk
-  static constexpr int GOFF = CF ? gq_of(NQC) : 1;  // vectors between lane groups
-  static constexpr int QOFF = CF ? 1 : 4;            // vectors between quad chunks
-  static constexpr int KCS = V * (CF ? row_cf(NQC) : row_compact(NQC));  // LDS row stride
-  static constexpr int VPR = KC / V;                // vectors per row per chunk
-  static constexpr int NV = ROWS * VPR;             // vectors per chunk
+  // LDS row layout of a staged operator of n quad chunks, in 16-byte vectors: a
+  // 16-byte LDS read serves 32 lanes at a time and is free of bank conflicts
+  // when their vectors are distinct modulo 32.  [g][quad chunk], the 4 lane groups
+  // GOFF vectors apart (odd) and rows 4 GOFF + 2 apart: 16 rows at a stride of 2
+  // mod 4 fill the even residues, the odd g offset the odd ones.
+  static constexpr int KC = G * NQ;               // staged k
+  static constexpr int GOFF = NQ | 1;             // vectors between lane groups
+  static constexpr int KCS = V * (4 * GOFF + 2);  // LDS row stride
+  static constexpr int VPR = KC / V;              // vectors per row
+  static constexpr int NV = ROWS * VPR;           // vectors per operator
   static constexpr int PER_THREAD = (NV + kThreads - 1) / kThreads;
-  // Prefetch the next offset's B vectors (a second register set) only where
-  // the registers allow it without spills.
-  static constexpr bool PREFETCH_B = P <= (sizeof(T) == 4 ? 8 : 7);
   static_assert(MS % V == 0, "multipole rows must hold whole vectors");
 };
 
@@ -151,10 +116,8 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
                                                   const T* __restrict__ ops,
                                                   T* __restrict__ out) {
   typedef Shape<P, T> S;
-  constexpr int NC = S::NC, RB = S::RB, RP = S::RP, MS = S::MS, V = S::V, G = S::G;
-  constexpr int NQ = S::NQ, NQC = S::NQC, NCH = S::NCH, KC = S::KC, KCS = S::KCS, KS = S::KS;
-  constexpr int RBM = S::RBM;
-  constexpr bool TAIL = S::TAIL;
+  constexpr int NC = S::NC, MS = S::MS, V = S::V, G = S::G;
+  constexpr int NQ = S::NQ, KCS = S::KCS, KS = S::KS, RBM = S::RBM;
   typedef typename Mfma<T>::acc_t acc_t;
   typedef typename Mfma<T>::vec_t vec_t;
   __shared__ __attribute__((aligned(16))) T sT[2][S::ROWS * KCS];
@@ -172,25 +135,22 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
   acc_t sum[RBM], comp[RBM], acc[RBM];
 #pragma unroll
   for (int r = 0; r < RBM; ++r) sum[r] = comp[r] = acc[r] = acc_t{0, 0, 0, 0};
-  // Tail row (TAIL): this lane's partial sum over its k values.
-  T tsum = T(0), tcomp = T(0), tacc = T(0);
 
   auto offset_of = [&](int i, int& dx, int& dy, int& dz) {
     return m2l::il_offset(pi, i, dx, dy, dz);
   };
-  // Operator chunk ch of operator op into registers / into an LDS buffer.
-  // Vector e of a chunk is row e / VPR, k-vector e % VPR; loads are clamped
-  // so that every lane issues the same loads.
-  auto stage_load = [&](int op, int ch, vec_t* reg) {
-    const T* base = ops + (size_t)op * RP * KS + ch * KC;
+  // Operator op into registers / into an LDS buffer.  Vector e of it is row
+  // e / VPR, k-vector e % VPR; loads are clamped so that every lane issues the
+  // same loads.
+  auto stage_load = [&](int op, vec_t* reg) {
+    const T* base = ops + (size_t)op * S::ROWS * KS;
 #pragma unroll
     for (int i = 0; i < S::PER_THREAD; ++i) {
       int e = tid + i * kThreads;
       e = e < S::NV ? e : S::NV - 1;
       const int row = e / S::VPR, kv = e % S::VPR;
-      const int k = ch * KC + kv * V;
-      // vectors past the operator's stored width (last chunk) read its last vector
-      const int kk = k + V <= KS ? kv * V : KS - V - ch * KC;
+      // vectors past the operator's stored width read its last vector
+      const int kk = kv * V + V <= KS ? kv * V : KS - V;
       reg[i] = *reinterpret_cast<const vec_t*>(base + (size_t)row * KS + kk);
     }
   };
@@ -200,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
       const int e = tid + i * kThreads;
       if (e < S::NV) {
         const int row = e / S::VPR, kv = e % S::VPR;  // kv = 4 (quad chunk) + g
-        *reinterpret_cast<vec_t*>(buf + row * KCS + ((kv % 4) * S::GOFF + (kv / 4) * S::QOFF) * V) =
+        *reinterpret_cast<vec_t*>(buf + row * KCS + ((kv % 4) * S::GOFF + kv / 4) * V) =
             reg[i];
       }
     }
@@ -221,26 +181,19 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
       b[q] = *reinterpret_cast<const vec_t*>(ms + k0);
     }
   };
-  // MFMAs of operator chunk ch (staged in buf) against B vectors b.
-  auto compute_chunk = [&](const T* buf, int ch, const vec_t* b) {
+  // MFMAs of the operator staged in buf against B vectors b.
+  auto compute = [&](const T* buf, const vec_t* b) {
     acc_t* dst = Mfma<T>::kChain ? acc : sum;
-    T& tdst = Mfma<T>::kChain ? tacc : tsum;
     const T* sa = buf + col * KCS + V * S::GOFF * kg;
-    const T* st = buf + (NC - 1) * KCS + V * S::GOFF * kg;  // tail row (same for all 16 columns)
-    vec_t av[2][RBM], at[2];
+    vec_t av[2][RBM];
 #pragma unroll
     for (int r = 0; r < RBM; ++r) av[0][r] = *reinterpret_cast<const vec_t*>(sa + 16 * r * KCS);
-    if (TAIL) at[0] = *reinterpret_cast<const vec_t*>(st);
 #pragma unroll
-    for (int qc = 0; qc < NQC; ++qc) {
-      const int q = ch * NQC + qc;
-      if (q >= NQ) break;
-      if (qc + 1 < NQC && q + 1 < NQ) {
+    for (int q = 0; q < NQ; ++q) {
+      if (q + 1 < NQ) {
 #pragma unroll
         for (int r = 0; r < RBM; ++r)
-          av[(qc + 1) & 1][r] =
-              *reinterpret_cast<const vec_t*>(sa + 16 * r * KCS + V * S::QOFF * (qc + 1));
-        if (TAIL) at[(qc + 1) & 1] = *reinterpret_cast<const vec_t*>(st + V * S::QOFF * (qc + 1));
+          av[(q + 1) & 1][r] = *reinterpret_cast<const vec_t*>(sa + 16 * r * KCS + V * (q + 1));
       }
       const int ns = (q == NQ - 1) ? S::S_LAST : V;
 #pragma unroll
@@ -248,15 +201,13 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
         if (s >= ns) break;
         const T bv = b[q][s];
 #pragma unroll
-        for (int r = 0; r < RBM; ++r) dst[r] = Mfma<T>::step(av[qc & 1][r][s], bv, dst[r]);
-        if (TAIL) tdst = fma(at[qc & 1][s], bv, tdst);
+        for (int r = 0; r < RBM; ++r) dst[r] = Mfma<T>::step(av[q & 1][r][s], bv, dst[r]);
       }
     }
   };
 
-  constexpr bool PB = S::PREFETCH_B;
   vec_t reg[S::PER_THREAD];
-  vec_t b0[NQ], b1[PB ? NQ : 1];
+  vec_t b0[NQ], b1[NQ];
   // Pipeline over the class's offsets: offset i is computed while the
   // operator of the next stage and the B vectors of offset i + 1 are loaded
   // and the source slot of offset i + 2 is looked up.
@@ -265,52 +216,35 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
   int nop = offset_of(1, ndx, ndy, ndz);
   Src s_cur = lookup(0, dx, dy, dz);
   Src s_next = lookup(1, ndx, ndy, ndz);
-  bool wave_any = false;
-  if (PB) {
-    load_b(row_of(s_cur), b0);
-    wave_any = __any(s_cur.ok);
-  }
-  stage_load(op, 0, reg);
+  load_b(row_of(s_cur), b0);
+  bool wave_any = __any(s_cur.ok);
+  stage_load(op, reg);
   stage_store(sT[0], reg);
   __syncthreads();
   int cur = 0;
 
-  // One offset: its NCH operator chunks; stages the next chunk (of this or the
-  // next offset) and, at the first chunk, prefetches the next offset's B
-  // vectors into bn (or, without prefetch, loads this offset's into bc).
-  // Returns false after the last offset.
+  // One offset; stages the next one's operator and prefetches its B vectors into
+  // bn.  Returns false after the last offset.
   auto do_offset = [&](vec_t* bc, vec_t* bn) -> bool {
     const bool more = i + 1 < kIL;
     int fdx, fdy, fdz;
     const int fi = i + 2 < kIL ? i + 2 : kIL - 1;
     const int fop = offset_of(fi, fdx, fdy, fdz);
     const Src s_far = lookup(fi, fdx, fdy, fdz);  // offset i + 2 (clamped at the end)
-    if (!PB) {
-      load_b(row_of(s_cur), bc);
-      wave_any = __any(s_cur.ok);
-    }
+    stage_load(more ? nop : op, reg);
+    load_b(row_of(s_next), bn);
+    if (wave_any) compute(sT[cur], bc);
+    if (Mfma<T>::kChain && wave_any) {
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      const bool last_chunk = ch == NCH - 1;
-      stage_load(last_chunk ? (more ? nop : op) : op, last_chunk ? 0 : ch + 1, reg);
-      if (PB && ch == 0) load_b(row_of(s_next), bn);
-      if (wave_any) compute_chunk(sT[cur], ch, bc);
-      if (Mfma<T>::kChain && last_chunk && wave_any) {
-#pragma unroll
-        for (int r = 0; r < RBM; ++r) {
-          Mfma<T>::add(sum[r], comp[r], acc[r]);
-          acc[r] = acc_t{0, 0, 0, 0};
-        }
-        if (TAIL) {
-          Mfma<T>::add1(tsum, tcomp, tacc);
-          tacc = T(0);
-        }
+      for (int r = 0; r < RBM; ++r) {
+        Mfma<T>::add(sum[r], comp[r], acc[r]);
+        acc[r] = acc_t{0, 0, 0, 0};
       }
-      if (last_chunk && !more) return false;
-      stage_store(sT[cur ^ 1], reg);
-      m2l::lds_barrier();
-      cur ^= 1;
     }
+    if (!more) return false;
+    stage_store(sT[cur ^ 1], reg);
+    m2l::lds_barrier();
+    cur ^= 1;
     ++i;
     op = nop;
     dx = ndx;
@@ -320,27 +254,14 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
     ndx = fdx;
     ndy = fdy;
     ndz = fdz;
-    if (PB) wave_any = __any(s_next.ok);
+    wave_any = __any(s_next.ok);
     s_cur = s_next;
     s_next = s_far;
     return true;
   };
-  if (PB) {
-    while (do_offset(b0, b1) && do_offset(b1, b0)) {
-    }
-  } else {
-    while (do_offset(b0, b0)) {
-    }
+  while (do_offset(b0, b1) && do_offset(b1, b0)) {
   }
 
-  // Tail row: combine the four lane groups' partials (fixed order; all lanes
-  // take part in the shuffles).
-  T tail = T(0);
-  if (TAIL) {
-    tail = tsum - tcomp;
-    tail += __shfl_xor(tail, 16);
-    tail += __shfl_xor(tail, 32);
-  }
   if (!col_ok) return;
   T* o = out + (tl.lvl_off + tl.target_slot(a)) * NC;
 #pragma unroll
@@ -350,7 +271,6 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
       const int row = 16 * r + Mfma<T>::row(kg, i);
       if (row < NC) o[row] = sum[r][i];
     }
-  if (TAIL && kg == 0) o[NC - 1] = tail;
 }
 
 template <int P>
