@@ -280,7 +280,7 @@ enum {
   FMM_PHASE_OPERATORS,  /* translation-operator tables */
   FMM_PHASE_P2M,
   FMM_PHASE_M2M,
-  FMM_PHASE_M2L,        /* the M2L kernel (FP64 and FP32 from p = 4: and the reordering of its source rows) */
+  FMM_PHASE_M2L,        /* the M2L kernel (FP64 / FP32 by reflections: and the reordering of its source rows) */
   FMM_PHASE_L2L,        /* adaptive tree: P2L included */
   FMM_PHASE_L2P,        /* adaptive tree: M2P included */
   FMM_PHASE_P2P,        /* near field, combination, unpermute, energy partials */

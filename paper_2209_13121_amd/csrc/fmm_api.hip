@@ -190,7 +190,7 @@ void prof_end(fmm_plan_s* P, hipStream_t s) {
 
 static hipError_t launch_m2l(fmm_plan_s* P, hipStream_t s) {
   if (P->m2l_np) return launch_m2l_bf16(P, s);
-  if (!sym::serves(P->p)) return launch_m2l_plain(P, s);
+  if (!P->m2l_sym) return launch_m2l_plain(P, s);
   return P->mixed ? launch_m2l_sym_f32(P, s) : launch_m2l_sym_f64(P, s);
 }
 
@@ -240,6 +240,7 @@ fmm_status plan_into(fmm_plan_s* P, const fmm_config& cfg, const Layout& lay, in
                      bool keep_operators) {
   // what a re-plan keeps: the operator tables in the workspace, profiling state
   const bool ops_ready = keep_operators && P->ops_ready;
+  const bool m2l_sym = keep_operators && P->m2l_sym;
   const uint32_t mask = keep_operators ? P->profile_mask : 0u;
   const int nevents = keep_operators ? P->nevents_created : 0;
   const int nrec = keep_operators ? P->nrec : 0;
@@ -256,6 +257,7 @@ fmm_status plan_into(fmm_plan_s* P, const fmm_config& cfg, const Layout& lay, in
   P->m2l_split = m2l_split;
   P->m2l_persistent = m2l_persistent;
   P->ops_ready = ops_ready;
+  P->m2l_sym = m2l_sym;
   P->profile_mask = mask;
   P->nevents_created = nevents;
   P->nrec = nrec;
@@ -280,9 +282,16 @@ fmm_status plan_into(fmm_plan_s* P, const fmm_config& cfg, const Layout& lay, in
   if (P->adaptive && (P->nlist[0] > lay.ucap || P->nlist[1] > lay.wcap || P->nlist[2] > lay.xcap))
     return FMM_E_WORKSPACE;  // the tree's lists do not fit the workspace's list capacity
   if (P->adaptive && launch_p2p_worklist(P, s) != hipSuccess) return FMM_E_DEVICE;
-  if (P->Ld >= 2 && !P->ops_ready) {
-    if (launch_operators(P, s) != hipSuccess) return FMM_E_DEVICE;
-    P->ops_ready = true;
+  if (P->Ld >= 2) {
+    // the M2L form follows the tree: a re-plan that changes it lays out the
+    // operators of the new one (adaptive trees only)
+    const bool was_sym = P->m2l_sym;
+    P->m2l_sym = !P->m2l_np && m2l_takes_sym(P);
+    if (!P->ops_ready || P->m2l_sym != was_sym) {
+      P->ops_ready = false;
+      if (launch_operators(P, s) != hipSuccess) return FMM_E_DEVICE;
+      P->ops_ready = true;
+    }
   }
   return FMM_OK;
 }

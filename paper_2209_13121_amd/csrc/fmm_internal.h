@@ -255,6 +255,7 @@ struct fmm_plan_s {
   int nevents_created;
   bool is_static;  // the per-device plan of fmm_evaluate_static (not freed by fmm_destroy)
   bool ops_ready;  // the workspace holds the translation operators of (p, kind)
+  bool m2l_sym;    // FP32 / FP64 M2L, and its operators: the reflection-reduced form
   // schedule (fmm_plan_set_schedule): work distribution only
   int p2p_persistent;  // adaptive P2P as a persistent kernel over the work-list
   int m2l_split;       // split-M2L tail work-groups per XCD (0 .. kM2lSplitPerXcd)
@@ -286,7 +287,8 @@ hipError_t fill_u32(uint32_t* a, int64_t n, uint32_t v, hipStream_t s);  // a[0.
 hipError_t launch_tree(fmm_plan_s* P, const double* d_pos, hipStream_t s);
 hipError_t launch_operators(fmm_plan_s* P, hipStream_t s);
 hipError_t launch_upward(fmm_plan_s* P, const double* d_q, hipStream_t s);
-hipError_t launch_m2l_plain(fmm_plan_s* P, hipStream_t s);  // FP32 / FP64, p <= 3
+hipError_t launch_m2l_plain(fmm_plan_s* P, hipStream_t s);  // FP32 / FP64, a product per offset
+bool m2l_takes_sym(fmm_plan_s* P);  // FP32 / FP64: the reflection-reduced form (m2l_form.h)
 hipError_t launch_m2l_bf16(fmm_plan_s* P, hipStream_t s);  // split forms (P->m2l_np > 0)
 hipError_t launch_m2m(fmm_plan_s* P, hipStream_t s);
 hipError_t launch_l2l(fmm_plan_s* P, hipStream_t s);

@@ -1,5 +1,6 @@
-// m2l.hip -- multipole-to-local translation on the FP32 / FP64 matrix cores up
-// to p = 3 (one 16-row block; higher orders: m2l_sym.h).
+// m2l.hip -- multipole-to-local translation on the FP32 / FP64 matrix cores, a
+// product per offset: up to p = 3, and up to p = 7 where it is faster than the
+// reflection-reduced form of m2l_sym.h (m2l_form.h has the rule).
 //
 // For a target box t at level l >= 2 the interaction list is every box s of
 // level l whose parent is adjacent to t's parent but which is not adjacent to
@@ -26,7 +27,7 @@
 //    the MFMAs of chunk q.  All 128 targets share each staged operator.
 //  * B operand (source coefficients): 16-byte vectors from global memory; a
 //    whole offset's vectors are prefetched while the previous offset's MFMAs
-////    run (two register sets used alternately).
+//    run (two register sets used alternately).
 //    Sources outside the domain read a zero row.  All loads are unconditional
 //    (clamped addresses) so the waits on them are exact.
 //  * FP32: each offset's product is a fresh MFMA chain and the chains are
@@ -37,6 +38,7 @@
 // Work-groups are assigned to XCDs in contiguous ranges so that neighbouring
 // tiles (which share operators and sources) share an L2.
 #include "m2l_common.h"
+#include "m2l_form.h"
 
 namespace fmm {
 namespace {
@@ -69,6 +71,12 @@ struct Mfma<float> {
     comp = (t - sum) - y;
     sum = t;
   }
+  static __device__ __forceinline__ void add1(float& sum, float& comp, float v) {
+    const float y = v - comp;
+    const float t = sum + y;
+    comp = (t - sum) - y;
+    sum = t;
+  }
 };
 template <>
 struct Mfma<double> {
@@ -81,15 +89,20 @@ struct Mfma<double> {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ void add(acc_t& sum, acc_t&, acc_t v) { sum += v; }
+  static __device__ __forceinline__ void add1(double& sum, double&, double v) { sum += v; }
 };
 
 // Static shape of the kernel for order P and type T.
 template <int P, typename T>
 struct Shape {
   static constexpr int NC = (P + 1) * (P + 1);
-  static_assert(NC <= 16, "one 16-row block");
-  static constexpr int RBM = 1;                // 16-row blocks
-  static constexpr int ROWS = 16;              // operator rows, staged in LDS
+  static constexpr int RB = (NC + 15) / 16;    // 16-row blocks
+  static constexpr int RP = RB * 16;
+  // NC = 16 RBM + 1 (p = 6): the last row is a per-lane dot product on the vector
+  // unit instead of a 16-row block holding one real row.
+  static constexpr bool TAIL = NC % 16 == 1 && NC > 16;
+  static constexpr int RBM = TAIL ? RB - 1 : RB;  // MFMA row blocks
+  static constexpr int ROWS = TAIL ? NC : RP;     // operator rows staged in LDS
   static constexpr int MS = mstride_of(NC);    // multipole row stride
   static constexpr int V = Mfma<T>::V;         // elements per vector
   static constexpr int G = 4 * V;              // k per quad chunk
@@ -108,6 +121,7 @@ struct Shape {
   static constexpr int NV = ROWS * VPR;           // vectors per operator
   static constexpr int PER_THREAD = (NV + kThreads - 1) / kThreads;
   static_assert(MS % V == 0, "multipole rows must hold whole vectors");
+  static_assert(2 * ROWS * KCS * (int)sizeof(T) <= 140 * 1024, "two staged operators beside the slot halo");
 };
 
 template <int P, typename T, bool AD>
@@ -117,7 +131,8 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
                                                   T* __restrict__ out) {
   typedef Shape<P, T> S;
   constexpr int NC = S::NC, MS = S::MS, V = S::V, G = S::G;
-  constexpr int NQ = S::NQ, KCS = S::KCS, KS = S::KS, RBM = S::RBM;
+  constexpr int NQ = S::NQ, KCS = S::KCS, KS = S::KS, RP = S::RP, RBM = S::RBM;
+  constexpr bool TAIL = S::TAIL;
   typedef typename Mfma<T>::acc_t acc_t;
   typedef typename Mfma<T>::vec_t vec_t;
   __shared__ __attribute__((aligned(16))) T sT[2][S::ROWS * KCS];
@@ -135,6 +150,8 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
   acc_t sum[RBM], comp[RBM], acc[RBM];
 #pragma unroll
   for (int r = 0; r < RBM; ++r) sum[r] = comp[r] = acc[r] = acc_t{0, 0, 0, 0};
+  // Tail row (TAIL): this lane's partial sum over its k values.
+  T tsum = T(0), tcomp = T(0), tacc = T(0);
 
   auto offset_of = [&](int i, int& dx, int& dy, int& dz) {
     return m2l::il_offset(pi, i, dx, dy, dz);
@@ -143,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
   // e / VPR, k-vector e % VPR; loads are clamped so that every lane issues the
   // same loads.
   auto stage_load = [&](int op, vec_t* reg) {
-    const T* base = ops + (size_t)op * S::ROWS * KS;
+    const T* base = ops + (size_t)op * RP * KS;
 #pragma unroll
     for (int i = 0; i < S::PER_THREAD; ++i) {
       int e = tid + i * kThreads;
@@ -184,16 +201,20 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
   // MFMAs of the operator staged in buf against B vectors b.
   auto compute = [&](const T* buf, const vec_t* b) {
     acc_t* dst = Mfma<T>::kChain ? acc : sum;
+    T& tdst = Mfma<T>::kChain ? tacc : tsum;
     const T* sa = buf + col * KCS + V * S::GOFF * kg;
-    vec_t av[2][RBM];
+    const T* st = buf + (NC - 1) * KCS + V * S::GOFF * kg;  // tail row (same for all 16 columns)
+    vec_t av[2][RBM], at[2];
 #pragma unroll
     for (int r = 0; r < RBM; ++r) av[0][r] = *reinterpret_cast<const vec_t*>(sa + 16 * r * KCS);
+    if (TAIL) at[0] = *reinterpret_cast<const vec_t*>(st);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       if (q + 1 < NQ) {
 #pragma unroll
         for (int r = 0; r < RBM; ++r)
           av[(q + 1) & 1][r] = *reinterpret_cast<const vec_t*>(sa + 16 * r * KCS + V * (q + 1));
+        if (TAIL) at[(q + 1) & 1] = *reinterpret_cast<const vec_t*>(st + V * (q + 1));
       }
       const int ns = (q == NQ - 1) ? S::S_LAST : V;
 #pragma unroll
@@ -202,6 +223,7 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
         const T bv = b[q][s];
 #pragma unroll
         for (int r = 0; r < RBM; ++r) dst[r] = Mfma<T>::step(av[q & 1][r][s], bv, dst[r]);
+        if (TAIL) tdst = fma(at[q & 1][s], bv, tdst);
       }
     }
   };
@@ -240,6 +262,10 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
         Mfma<T>::add(sum[r], comp[r], acc[r]);
         acc[r] = acc_t{0, 0, 0, 0};
       }
+      if (TAIL) {
+        Mfma<T>::add1(tsum, tcomp, tacc);
+        tacc = T(0);
+      }
     }
     if (!more) return false;
     stage_store(sT[cur ^ 1], reg);
@@ -262,6 +288,14 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
   while (do_offset(b0, b1) && do_offset(b1, b0)) {
   }
 
+  // Tail row: combine the four lane groups' partials (fixed order; all lanes
+  // take part in the shuffles).
+  T tail = T(0);
+  if (TAIL) {
+    tail = tsum - tcomp;
+    tail += __shfl_xor(tail, 16);
+    tail += __shfl_xor(tail, 32);
+  }
   if (!col_ok) return;
   T* o = out + (tl.lvl_off + tl.target_slot(a)) * NC;
 #pragma unroll
@@ -271,6 +305,7 @@ __global__ __launch_bounds__(kThreads) void k_m2l(m2l::Args a, const T* __restri
       const int row = 16 * r + Mfma<T>::row(kg, i);
       if (row < NC) o[row] = sum[r][i];
     }
+  if (TAIL && kg == 0) o[NC - 1] = tail;
 }
 
 template <int P>
@@ -280,24 +315,36 @@ struct M2LRun {
     const m2l::Args a = m2l::make_args(Pl);
     const unsigned grid = m2l::grid_of(a);
     if (Pl->mixed)
-      go<float>(Pl, a, grid, wsp<float>(Pl, lay.mult32), wsp<float>(Pl, lay.zero_row),
-                wsp<float>(Pl, lay.op_m2l32), wsp<float>(Pl, lay.m2l_out), s);
-    else
-      go<double>(Pl, a, grid, wsp<double>(Pl, lay.mult64), wsp<double>(Pl, lay.zero_row),
-                 wsp<double>(Pl, lay.op_m2l64), wsp<double>(Pl, lay.m2l_out), s);
-    return hipGetLastError();
+      return go<float>(Pl, a, grid, wsp<float>(Pl, lay.mult32), wsp<float>(Pl, lay.zero_row),
+                       wsp<float>(Pl, lay.op_m2l32), wsp<float>(Pl, lay.m2l_out), s);
+    return go<double>(Pl, a, grid, wsp<double>(Pl, lay.mult64), wsp<double>(Pl, lay.zero_row),
+                      wsp<double>(Pl, lay.op_m2l64), wsp<double>(Pl, lay.m2l_out), s);
   }
+  // Only the instances that the rule can choose
   template <typename T>
-  static void go(fmm_plan_s* Pl, const m2l::Args& a, unsigned grid, const T* mult, const T* zero,
-                 const T* ops, T* out, hipStream_t s) {
-    if (Pl->adaptive)
-      k_m2l<P, T, true><<<grid, kThreads, 0, s>>>(a, mult, zero, ops, out);
-    else
-      k_m2l<P, T, false><<<grid, kThreads, 0, s>>>(a, mult, zero, ops, out);
+  static hipError_t go(fmm_plan_s* Pl, const m2l::Args& a, unsigned grid, const T* mult, const T* zero,
+                       const T* ops, T* out, hipStream_t s) {
+    constexpr bool fp64 = sizeof(T) == 8;
+    if (Pl->adaptive) {
+      if constexpr (!sym::serves(P, fp64, true, INT32_MAX, 1)) {
+        k_m2l<P, T, true><<<grid, kThreads, 0, s>>>(a, mult, zero, ops, out);
+        return hipGetLastError();
+      }
+    } else {
+      if constexpr (!sym::serves(P, fp64, false, INT32_MAX, 1)) {
+        k_m2l<P, T, false><<<grid, kThreads, 0, s>>>(a, mult, zero, ops, out);
+        return hipGetLastError();
+      }
+    }
+    return hipErrorInvalidValue;
   }
 };
 
 }  // namespace
+
+bool m2l_takes_sym(fmm_plan_s* P) {
+  return sym::serves(P->p, !P->mixed, P->adaptive, m2l::make_args(P, 16).ngroups, m2l::make_args(P).ngroups);
+}
 
 hipError_t launch_m2l_plain(fmm_plan_s* P, hipStream_t s) {
   prof_begin(P, FMM_PHASE_M2L, s);
@@ -307,6 +354,10 @@ hipError_t launch_m2l_plain(fmm_plan_s* P, hipStream_t s) {
     case 1: e = M2LRun<1>::run(P, s); break;
     case 2: e = M2LRun<2>::run(P, s); break;
     case 3: e = M2LRun<3>::run(P, s); break;
+    case 4: e = M2LRun<4>::run(P, s); break;
+    case 5: e = M2LRun<5>::run(P, s); break;
+    case 6: e = M2LRun<6>::run(P, s); break;
+    case 7: e = M2LRun<7>::run(P, s); break;
   }
   prof_end(P, s);
   return e;

@@ -1,4 +1,4 @@
-// m2l_sym.h -- tables of the reflection-reduced M2L (m2l_sym.hip): the parity
+// m2l_sym.h -- tables of the reflection-reduced M2L (m2l_sym_kernel.h): the parity
 // classes of the packed real coefficients, the order of rows and columns they
 // give, and the offsets grouped into orbits.
 //
@@ -17,6 +17,7 @@
 #pragma once
 
 #include "fmm_internal.h"
+#include "m2l_form.h"
 
 namespace fmm {
 namespace sym {
@@ -30,14 +31,6 @@ __host__ __device__ constexpr int parity_of(int c) {
   const int im = r != 0 && r % 2 == 0 ? 1 : 0;
   return ((n + m) & 1) | im << 1 | ((m + im) & 1) << 2;
 }
-
-// The smallest order it serves: rows are padded to 16 per class, so an output
-// column costs row blocks x orbits, 8 .. 15 blocks x 39.5 against
-// ceil(ncoef / 16) x 189 without reflections; up to p = 3 one block holds every
-// row and the plain form (m2l.hip) is cheaper (measured at 2^20 charges, depth
-// 6, p 3, FP64: 1.0 ms against 1.2 ms for its best form here).
-constexpr int kMinP = 4;
-inline bool serves(int p) { return p >= kMinP; }
 
 constexpr int kNumOps = 56;  // orbits of the 316 offsets = items of a target's loop
 

@@ -689,10 +689,6 @@ __global__ __launch_bounds__(kBlock) void k_sym_rows(Tab tab, int str, int64_t b
   }
 }
 
-// Fewest work-groups of the wide forms: with fewer the small form is used, its
-// 8 x more work-groups then fill the chip better.
-constexpr int64_t kWideGroups = 200;
-
 // Work-groups that share 16 targets in the small form, with the work-groups
 // (of one each) that there are.  Two, each walking half of the 56 items (4
 // instead of 7 a wave) and adding to zeroed results (two terms: the order does
@@ -731,8 +727,10 @@ hipError_t run(fmm_plan_s* Pl, hipStream_t s) {
   };
   constexpr int W = gather_waves(P);
   if (wide && !Pl->adaptive) {
-    share(8);
-    k_m2l_block<P, T><<<m2l::grid_of(a), kSymThreads, 0, s>>>(a, rows, ops, out);
+    if constexpr (serves(P, sizeof(T) == 8, false, INT32_MAX, 1)) {
+      share(8);
+      k_m2l_block<P, T><<<m2l::grid_of(a), kSymThreads, 0, s>>>(a, rows, ops, out);
+    }
   } else {
     if (wide) share(W);
     if (parts == 2) a.ngroups *= 2;

@@ -454,7 +454,7 @@ hipError_t launch_operators(fmm_plan_s* P, hipStream_t s) {
       k_gen_m2l_bf<2><<<kNumM2LOps, kBlock, 0, s>>>(P->p, P->adaptive, ob);
     else
       k_gen_m2l_bf<3><<<kNumM2LOps, kBlock, 0, s>>>(P->p, P->adaptive, ob);
-  } else if (sym::serves(P->p)) {
+  } else if (P->m2l_sym) {
     const sym::Tab tab = sym::make_tab(P->p);
     const unsigned grid = sym::kNumOps * kSymSplit;
     if (P->mixed)
