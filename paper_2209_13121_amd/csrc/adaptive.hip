@@ -565,6 +565,13 @@ __global__ __launch_bounds__(64) void k_p2l(ATree t, const uint32_t* __restrict_
 //   d/dy      += Im(M_N^{m-1} z) + Im(M_N^{m+1} z)
 //   d/dz      -= w Re(M_N^m z)            w = 1 for m = 0, else 2
 constexpr int kM2pWaves = 4;
+// Orders the LDS accesses of a wave's lanes before it with those after it: the
+// barrier alone orders instructions, not memory.  (Neither emits an instruction.)
+__device__ __forceinline__ void wave_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 template <int P, typename T>
 __global__ __launch_bounds__(64 * kM2pWaves, 2) void k_m2p(ATree t, const uint32_t* __restrict__ wbox,
                                                            const Rec<T>* __restrict__ src, int64_t n,
@@ -615,7 +622,7 @@ __global__ __launch_bounds__(64 * kM2pWaves, 2) void k_m2p(ATree t, const uint32
         const uint32_t x = lane + 64 * i;
         if (x < 4 * MS) mw[x] = nx[i];
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_exchange();
       const int lw = t.level[w];  // > l
       int wc[3];
       unpack_coord(t.coord[w], wc[0], wc[1], wc[2]);
@@ -664,7 +671,7 @@ __global__ __launch_bounds__(64 * kM2pWaves, 2) void k_m2p(ATree t, const uint32
       g[0] += inv_hw * inv_hw * (double)gx;
       g[1] += inv_hw * inv_hw * (double)gy;
       g[2] -= inv_hw * inv_hw * (double)(gz0 + T(2) * gz1);
-      __builtin_amdgcn_wave_barrier();
+      wave_exchange();
     }
     double v[4] = {phi, g[0], g[1], g[2]};
 #pragma unroll
