@@ -16,7 +16,7 @@ constexpr int kSortChunk = 4 * kBlock;
 constexpr int kSortCoarse = 512;
 inline bool sort_two_level(int L) { return L >= 3 && L <= 7; }
 inline int64_t sort_hist_elems(int64_t n) {
-  return (int64_t)kSortCoarse * ((n + kSortChunk - 1) / kSortChunk) + 1;
+  return (int64_t)kSortCoarse * ((n + kSortChunk - 1) / kSortChunk);
 }
 constexpr int kNumM2LOps = 316;      // offsets in [-3,3]^3 \ [-1,1]^3
 constexpr int kIL = 189;             // interaction-list offsets per parity class

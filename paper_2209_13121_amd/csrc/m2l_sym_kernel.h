@@ -22,7 +22,8 @@
 //    halo) lies in LDS, copied there once per chunk while the previous one is
 //    used; an orbit's sources are LDS reads at uniform displacements.
 //  * k_m2l_gather (adaptive tree): the same 16 parents per work-group, sources
-//    read from global memory through the source table.
+//    read from global memory through the source table.  (Many targets at p 4 to 6,
+//    FP32 also 7: the plain form, m2l_form.h.)
 //  * k_m2l_gather, small (few targets, where the others leave most of the
 //    chip idle): the waves of a work-group share 16 targets of one
 //    class and split the items (wave w takes w, w + W, ...), operators are read
@@ -32,9 +33,9 @@
 // Sources outside the domain (or absent) read row 0, which is zero.
 //
 // Bound (FP64, 2^20 charges, depth 6, p = 8): the matrix cores and the vector
-// unit, which share the FP64 pipe: 1.24e8 v_mfma_f64_16x16x4 (64 cycles each;
-// 128 padded rows of 81 real) are 3.7 ms and the signed sums 1.2 ms of the
-// block form's 5.9 ms; the kernel with a product per offset took 13.2 ms
+// unit, which share the FP64 pipe: 1.30e8 v_mfma_f64_16x16x4 (64 cycles each;
+// 128 padded rows of 81 real) are 3.8 ms and the signed sums 1.2 ms of the
+// block form's 5.9 ms (0.83 of its cycles, counters); the kernel with a product per offset took 13.2 ms
 // (depth 5: 2.70 -> 1.20 ms; 2 x 10^5 charges, depth 5, p = 12: 17.5 -> 4.2
 // ms; depth 4, small form: 1.31 -> 0.32 ms; clusters, 3 x 10^5 sites, p = 10:
 // 3.2 -> 1.6 ms).  Operators through LDS with a barrier per step: 9.1 ms (the
@@ -426,7 +427,9 @@ __global__ __launch_bounds__(kSymThreads, 2) void k_m2l_block(m2l::Args a, const
         has_source(code, cls, src) ? -(d[0] * str[0] + d[1] * str[1] + d[2] * str[2]) : kNoSource;
   }
   // the operator of the next step arrives during this one in a second set of
-  // registers where there is room for one
+  // registers, up to 9 row blocks (p = 9).  VGPRs spilled of 256: FP64 none to p = 10,
+  // then 28 and 54 without the second set; FP32, whose chains have their own sums,
+  // 9 to 16 at p 4 .. 9, then 51, 110 and 501 without it
   constexpr int AHEAD = NB <= 9 ? 1 : 0;
   vec_t xv[NCLS], av[1 + AHEAD][NB];
   int disp[NCLS];
@@ -546,9 +549,9 @@ struct Target {
 // some 50 registers fewer (FP64: none spilled; with seven, 15 at p = 10, 361 at
 // p = 12).  FP64, ms, seven bodies -> one: 262 144 charges, depth 4, p = 4 / 8 / 10 /
 // 12: 0.138 / 0.331 / 0.495 / 3.61 -> 0.132 / 0.321 / 0.463 / 1.12; adaptive, 10^6,
-// p = 6 / 10: 1.65 / 4.22 -> 1.55 / 3.98.  FP32 has registers to spare up to p = 10,
+// p = 10: 4.22 -> 3.98.  FP32 spills little up to p = 10 (15 at p = 4, 8 at p = 10),
 // and there the products that a known axis leaves out by class weigh more (10^6,
-// p = 6 / 10: 0.98 / 2.00 against 1.08 / 2.22); p = 12: 0.72 -> 0.67.
+// p = 10: 2.00 against 2.22); p = 12: 0.72 -> 0.67.
 template <int P, typename T>
 constexpr bool any_zeros() {
   return sizeof(T) == 8 || P >= 11;

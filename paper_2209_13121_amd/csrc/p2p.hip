@@ -31,9 +31,10 @@
 // fixed tree order over the per-particle terms.
 //
 // Bound: vector issue.  A mixed pair is 17 instructions (3 FP64 subtractions,
-// 3 conversions, 1 / r at half rate) and the loop adds 0.75 at K = 4: 81 cycles
-// for 64 pairs.  Measured (uniform): 2^20 charges, depth 4 (256 a leaf), mixed
-// 3.87 ms where 81 cycles for every pair would take 3.4 (FP32 hi + lo pair
+// 3 conversions, 1 / r at half rate), 19 with the loop and idle lanes: 80 cycles for
+// 64 pairs, 90 % of the launch (FP64: 19 and 21, 96 cycles, 73 %; counters).
+// Measured (uniform): 2^20 charges, depth 4 (256 a leaf), mixed
+// 3.87 ms (FP32 hi + lo pair
 // offsets and a lane layout of one target per lane up to 32 targets, K = 1, 2,
 // 4 above: 4.65 ms), FP64 5.8 ms (1 / sqrt by square root and division, 2 waves
 // per SIMD: 13.9 ms); 10^5 charges, depth 4 (24 a leaf), mixed 96 -> 67 us;
@@ -77,10 +78,12 @@ struct Acc {
 __device__ __forceinline__ Tgt make_tgt(const Rec<double>& r) { return Tgt{r.x, r.y, r.z}; }
 
 __device__ __forceinline__ float inv_sqrt(float x) { return __builtin_amdgcn_rsqf(x); }
-// FP64: the hardware estimate y (about 2^-26) and one step of third order:
-// with e = 1 - x y^2, x^(-1/2) = y (1 + e / 2 + 3 e^2 / 8 + ...), the dropped
-// term below 2^-78; 6 instructions instead of the 30 of a square root and a
-// division (4 waves per SIMD instead of 2 as well).
+// FP64: the hardware estimate y (relative error up to 2^-24.2 over 4 10^6 values)
+// and one step of third order: with e = 1 - x y^2, below 2^-23.2,
+// x^(-1/2) = y (1 + e / 2 + 3 e^2 / 8 + ...), the dropped term 5 e^3 / 16 below
+// 2^-71.  Relative error at most 1.25 2^-53, 0.41 in the mean, against 1.49 and 0.50
+// of 1 / sqrt(x); 6 instructions instead of the 30 of a square root and a division
+// (and 3 waves per SIMD instead of 2).
 __device__ __forceinline__ double inv_sqrt(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   const double e = fma(-(x * y), y, 1.0);
@@ -775,9 +778,10 @@ hipError_t launch_near_and_finish(fmm_plan_s* P, double* d_phi, double* d_force,
     prof_begin(P, FMM_PHASE_ENERGY, s);
     const int64_t nparts = (n + 4 * kBlock - 1) / (4 * kBlock);
     double* part = eterm + n;
-    // few terms: one block sums them alone (4096: 5.5 us against 9.1 for the two
-    // launches; 10 007: 11.2 against 9.2).  A last block that adds the block sums
-    // in one launch was slower: the fences of 1024 blocks took 9 to 27 us.
+    // few terms: one block sums them alone (us between events, one / two launches:
+    // 700 terms 6.0 / 8.0, 3000 6.8 / 8.1, 4096 8.0 / 8.2, 5000 8.7 / 8.1, 8192
+    // 11.9 / 8.2).  A last block that adds the block sums in one launch was slower: the
+    // fences of 1024 blocks took 9 to 27 us.
     if (n <= 16 * kBlock) {
       k_energy<<<1, kBlock, 0, s>>>(eterm, n, d_energy);
     } else {

@@ -569,7 +569,7 @@ hipError_t launch_tree(fmm_plan_s* P, const double* d_pos, hipStream_t s) {
     constexpr int64_t kFoldBlocks = 32;
     const bool fold = nblk <= kFoldBlocks;
     if (!fold) {
-      const int64_t nh = kSortCoarse * nblk;
+      const int64_t nh = sort_hist_elems(n);
       hipError_t e = scan_exclusive(hist, nh, nh, hist, wsp<uint32_t>(P, lay.scan_tmp), s);
       if (e != hipSuccess) return e;
     }
