@@ -157,7 +157,9 @@ fmm_status fmm_plan(const fmm_config *cfg, int64_t n, const double *d_pos, void 
  * order; the same n and configuration), keeping the translation operators
  * already in the plan's workspace: they depend on p and the M2L form only, so
  * a sequence of position sets (time steps of a simulation) generates them
- * once.  Everything else is as for fmm_plan (the tree build, the adaptive
+ * once (adaptive trees with an FP64 / FP32 M2L and p 4 to 7: those of the M2L
+ * again when the number of boxes makes another form the faster one).
+ * Everything else is as for fmm_plan (the tree build, the adaptive
  * tree's read-backs); charges of an earlier fmm_evaluate are forgotten; the
  * profiling selection and unread profile records are kept.  Errors: FMM_E_INVALID_ARG (plan or
  * d_pos NULL), FMM_E_WORKSPACE (adaptive lists over capacity), FMM_E_DEVICE. */

@@ -288,9 +288,9 @@ fmm_status plan_into(fmm_plan_s* P, const fmm_config& cfg, const Layout& lay, in
     const bool was_sym = P->m2l_sym;
     P->m2l_sym = !P->m2l_np && m2l_takes_sym(P);
     if (!P->ops_ready || P->m2l_sym != was_sym) {
-      P->ops_ready = false;
-      if (launch_operators(P, s) != hipSuccess) return FMM_E_DEVICE;
-      P->ops_ready = true;
+      const hipError_t oe = launch_operators(P, s);
+      P->ops_ready = oe == hipSuccess;
+      if (oe != hipSuccess) return FMM_E_DEVICE;
     }
   }
   return FMM_OK;

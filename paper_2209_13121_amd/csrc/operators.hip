@@ -426,7 +426,8 @@ hipError_t launch_operators(fmm_plan_s* P, hipStream_t s) {
   const Layout& lay = P->lay;
   prof_begin(P, FMM_PHASE_OPERATORS, s);
   const int kp = shift_kpad(P->nc), rp = m2l_rows_pad(P->p);
-  k_gen_shift<<<16 * kShiftSplit, kBlock, 0, s>>>(P->p, kp, rp, wsp<double>(P, lay.op_m2m),
+  if (!P->ops_ready)  // (a plan that only changes its M2L form has them)
+    k_gen_shift<<<16 * kShiftSplit, kBlock, 0, s>>>(P->p, kp, rp, wsp<double>(P, lay.op_m2m),
                                     wsp<double>(P, lay.op_l2l));
   if (P->m2l_f16) {
     const int nc = P->nc, rpp = m2lb_rows(nc), kp = 32 * m2lb_ksteps(nc);

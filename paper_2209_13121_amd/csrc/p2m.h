@@ -100,7 +100,9 @@ __device__ __forceinline__ void p2m_box(const Rec<double>* __restrict__ src, uin
 // 27 / 37; 256 per leaf: 16 / 32 / 64 lanes 26 / 30 / 40), and more where that leaves
 // SIMDs without a wave (4096 leaves of 24: 4 / 16 lanes 12.8 / 9.6; adaptive, 6208
 // boxes of 23: 22 / 14; 512 leaves of 2048: 16 / 64 lanes 120 / 38; but 10 952 boxes
-// of 7: 4 / 16 lanes 10.5 / 13.4).
+// of 7: 4 / 16 lanes 10.5 / 13.4; where most boxes hold about one particle more lanes
+// lose a little, 4096 leaves of 0.7, p = 8: 1 / 16 lanes 8.5 / 9.4, and where few of
+// them hold all they win by far, so the rule stays with the mean).
 inline int p2m_lanes(int64_t n, int64_t nbox) {
   constexpr int64_t kFullLanes = 40000;
   const int steps[5] = {1, 2, 4, 16, 64};
